@@ -191,23 +191,31 @@ __global__ __launch_bounds__(kThreads) void gemm_nt_kernel(GemmArgs g, int batch
 }
 
 // ---------------------------------------------------------------------------
-// bf16 "NT" GEMM through LDS DMA (both operands reduction-contiguous, 16-byte
-// aligned rows, Kred a multiple of 8).  The MFMA's A operand is a row of B
+// "NT" GEMM through LDS DMA (both operands reduction-contiguous, 16-byte
+// aligned rows, Kred whole 16-byte units).  The MFMA's A operand is a row of B
 // (a pixel of IM2COL's column matrix, a Winograd tile) and its B operand a
 // row of A (a filter), so each lane ends with four consecutive j of one i:
 // the output row's order.
 //
 // A workgroup (4 waves, WJ x WI) owns TJ rows of B x TI rows of A and walks
-// the reduction in k-tiles of 64.  A k-tile stage is the TJ + TI rows of 128
-// bytes, two rows per 256-byte line with the 16-byte unit u of row r at
-// position 8 (r & 1) + (u ^ ((r >> 1) & 7)) of line r >> 1, so 16 lanes
-// reading one unit of 16 consecutive rows hit 16 distinct bank groups.  The
-// stage is filled by `buffer_load ... lds` (no register round trip): DMA
-// instruction J writes the stage's 16-byte units J*64 .. J*64+63, and each
-// lane fetches the unit that the layout puts at its place (rows past the
-// operand and reduction elements past Kred read zeros through the buffer
-// range).  NST stages form a ring with NST - 1 k-tiles in flight and one
-// barrier per k-tile.
+// the reduction in k-tiles of 128 bytes (64 bf16, 32 fp32).  A k-tile stage
+// is the TJ + TI rows of 128 bytes, two rows per 256-byte line with the
+// 16-byte unit u of row r at position 8 (r & 1) + (u ^ ((r >> 1) & 7)) of line
+// r >> 1, so 16 lanes reading one unit of 16 consecutive rows hit 16 distinct
+// bank groups.  The stage is filled by `buffer_load ... lds` (no register
+// round trip): DMA instruction J writes the stage's 16-byte units J*64 ..
+// J*64+63, and each lane fetches the unit that the layout puts at its place
+// (rows past the operand and reduction elements past Kred read zeros through
+// the buffer range).  NST stages form a ring with NST - 1 k-tiles in flight
+// and one barrier per k-tile.
+//
+// What bounds it: short reductions (4 to 18 k-tiles) make the first tile's
+// latency and the epilogue half of a workgroup's time, so what counts is how
+// many workgroups share a CU: two stages, 32 or 48 KiB of LDS, 5 or 3
+// workgroups per CU for the 64 x 64 and 128 x 64 tiles.  VGG's 256 -> 256
+// 56 x 56 fp32 layer (Winograd, 16 products of 256 x 6272 x 256): 160 us with
+// the register-staged kernel above, 195 (four stages, 64 x 64), 130 (two
+// stages); the fp32 matrix units' own time is 86 us.
 template <int TJ, int TI, int WJ_>
 struct GemmDmaShape {
   static constexpr int WJ = WJ_;
@@ -215,29 +223,38 @@ struct GemmDmaShape {
   static constexpr int MJ = TJ / WJ / 32, NI = TI / WI / 32;  // 32 x 32 blocks per wave
   static constexpr int ROWS = TJ + TI;
   static constexpr int STAGE = ROWS * 128;
-  static constexpr int NST = 3 * STAGE <= 96 * 1024 ? 4 : 3;
+    static constexpr int NST = STAGE <= 24 * 1024 ? 2 : 3;
   static constexpr int NDMA = ROWS / 8 / 4;  // DMA instructions per wave and stage
   static_assert(WJ * WI == 4 && MJ >= 1 && NI >= 1 && TJ % 32 == 0 && TI % 32 == 0 && ROWS % 32 == 0, "tile");
   static_assert(NST * STAGE <= 160 * 1024 && NDMA * (NST - 1) <= 63, "stages");
 };
 
-template <int TJ, int TI, int WJ, bool OUT_F32>
-__global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs g, int batch_base, uint32_t a_bytes,
+template <typename T, int TJ, int TI, int WJ, bool OUT_F32>
+__global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs g, int njt, int nit, uint32_t a_bytes,
                                                        uint32_t b_bytes) {
   using Sh = GemmDmaShape<TJ, TI, WJ>;
   constexpr int MJ = Sh::MJ, NI = Sh::NI, NST = Sh::NST, NDMA = Sh::NDMA, STAGE = Sh::STAGE;
+  constexpr int ES = elem<T>::bytes, UE = elem<T>::per16, BK = 128 / ES;  // a k-tile is 128 bytes of a row
   extern __shared__ __align__(16) vec16 smem[];
   char* lds = reinterpret_cast<char*>(smem);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wj = wave % Sh::WJ, wi = wave / Sh::WJ;
-  const int j0 = blockIdx.x * TJ, i0 = blockIdx.y * TI;
-  const int b = batch_base + blockIdx.z;
+  // Work units (batch item, j tile, i tile; i fastest) are dealt to the eight
+  // XCDs in contiguous ranges (workgroup w runs on XCD w % 8): the i tiles
+  // that read one j tile's rows of B follow each other on one L2.
+  const int units = njt * nit * g.batch;
+  const int per_xcd = (units + 7) >> 3;
+  const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (unit >= units || static_cast<int>(blockIdx.x >> 3) >= per_xcd) return;  // uniform
+  const int jt = unit / nit;
+  const int b = jt / njt;
+  const int j0 = (jt - b * njt) * TJ, i0 = (unit - jt * nit) * TI;
   const int b0 = b / g.bdiv, b1 = b - b0 * g.bdiv;
-  const bf16_t* A = reinterpret_cast<const bf16_t*>(g.A) + b0 * g.sA0 + b1 * g.sA1;
-  const bf16_t* B = reinterpret_cast<const bf16_t*>(g.B) + b0 * g.sB0 + b1 * g.sB1;
-  const __amdgpu_buffer_rsrc_t ar = make_rsrc(A, a_bytes);
-  const __amdgpu_buffer_rsrc_t br = make_rsrc(B, b_bytes);
+  const T* A = reinterpret_cast<const T*>(g.A) + b0 * g.sA0 + b1 * g.sA1;
+  const T* B = reinterpret_cast<const T*>(g.B) + b0 * g.sB0 + b1 * g.sB1;
+  const u32x4_t ar = dma_rsrc(A, a_bytes), br = dma_rsrc(B, b_bytes);
+  const uint32_t lds0 = lds_address(lds);
 
   // This wave's DMA instructions: J = wave * NDMA + d.  Instructions below
   // TJ / 8 fill rows of B, the rest rows of A (a row boundary never falls
@@ -253,21 +270,20 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs g, int batch_bas
     const int grow = isb ? j0 + row : i0 + row - TJ;
     const bool ok = grow < (isb ? g.N : g.M);
     const int64_t ld = isb ? g.ldb : g.lda;
-    dvo[d] = ok ? static_cast<uint32_t>((grow * ld + u * 8) * 2) : (isb ? b_bytes : a_bytes);
-    dku[d] = u * 8;
+    dvo[d] = ok ? static_cast<uint32_t>((grow * ld + u * UE) * ES) : (isb ? b_bytes : a_bytes);
+    dku[d] = u * UE;
   }
-  const int nk = (g.Kred + 63) / 64;
+  const int nk = (g.Kred + BK - 1) / BK;
   auto issue = [&](int kt) {
-    char __attribute__((address_space(3)))* st =
-        (char __attribute__((address_space(3)))*)(lds + (kt % NST) * STAGE);
+    const uint32_t st = lds0 + (kt % NST) * STAGE;
     const uint32_t so = static_cast<uint32_t>(kt) * 128;
-    const bool tail = (kt + 1) * 64 > g.Kred;
+    const bool tail = (kt + 1) * BK > g.Kred;
 #pragma unroll
     for (int d = 0; d < NDMA; ++d) {
       const int J = wave * NDMA + d;
       const bool isb = J < TJ / 8;
-      const uint32_t vo = (!tail || kt * 64 + dku[d] < g.Kred) ? dvo[d] : (isb ? b_bytes : a_bytes);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(isb ? br : ar, (lds_void_t*)(st + J * 1024), 16, vo, so, 0, 0);
+      const uint32_t vo = (!tail || kt * BK + dku[d] < g.Kred) ? dvo[d] : (isb ? b_bytes : a_bytes);
+      dma16(isb ? br : ar, st + J * 1024, vo, so);
     }
   };
 
@@ -303,31 +319,41 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs g, int batch_bas
     asm volatile("" ::: "memory");
     if (kt + NST - 1 < nk) issue(kt + NST - 1);  // into the stage of tile kt - 1
     const char* st = lds + (kt % NST) * STAGE;
-    bf16x8_t fa[2][MJ], fb[2][NI];
+    vec16 fa[2][MJ], fb[2][NI];
     auto read = [&](auto t_c) {
       constexpr int t = decltype(t_c)::value;
 #pragma unroll
-      for (int mj = 0; mj < MJ; ++mj) fa[t & 1][mj] = *reinterpret_cast<const bf16x8_t*>(st + aoff[mj][t]);
+      for (int mj = 0; mj < MJ; ++mj) fa[t & 1][mj] = *reinterpret_cast<const vec16*>(st + aoff[mj][t]);
 #pragma unroll
-      for (int ni = 0; ni < NI; ++ni) fb[t & 1][ni] = *reinterpret_cast<const bf16x8_t*>(st + boff[ni][t]);
+      for (int ni = 0; ni < NI; ++ni) fb[t & 1][ni] = *reinterpret_cast<const vec16*>(st + boff[ni][t]);
     };
     read(std::integral_constant<int, 0>{});
     static_for<4>([&](auto t_c) {
       constexpr int t = decltype(t_c)::value;
       if constexpr (t + 1 < 4) read(std::integral_constant<int, t + 1>{});
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (sizeof(T) == 4) {
 #pragma unroll
-      for (int mj = 0; mj < MJ; ++mj)
+        for (int d = 0; d < 4; ++d)
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-          acc[mj][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[t & 1][mj], fb[t & 1][ni], acc[mj][ni], 0, 0, 0);
+          for (int mj = 0; mj < MJ; ++mj)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+              acc[mj][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fa[t & 1][mj].d[d]),
+                                                                 __uint_as_float(fb[t & 1][ni].d[d]), acc[mj][ni], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int mj = 0; mj < MJ; ++mj)
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni) mfma_32x32<T>(acc[mj][ni], fa[t & 1][mj], fb[t & 1][ni]);
+      }
       __builtin_amdgcn_sched_barrier(0);
     });
   }
 
   // Epilogue: bias (per i), ReLU, four consecutive j per store.
   const int64_t cofs = b0 * g.sC0 + b1 * g.sC1;
-  const bf16_t* bias = g.bias ? reinterpret_cast<const bf16_t*>(g.bias) + b1 * g.sBias1 : nullptr;
+  const T* bias = g.bias ? reinterpret_cast<const T*>(g.bias) + b1 * g.sBias1 : nullptr;
   const bool vst = ((cofs | g.ldc | g.sCj) & 3) == 0 && (g.jspan == 0 || g.jspan % 4 == 0) &&
                    reinterpret_cast<uintptr_t>(g.C) % 16 == 0;
   // Offset of column j in C (a folded batch maps j to its item's columns).
@@ -340,7 +366,7 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs g, int batch_bas
   for (int ni = 0; ni < NI; ++ni) {
     const int i = i0 + (wi * NI + ni) * 32 + l32;
     if (i >= g.M) continue;
-    const float bv = bias ? elem<bf16_t>::load(bias + i) : 0.f;
+    const float bv = bias ? elem<T>::load(bias + i) : 0.f;
     const int64_t row = cofs + static_cast<int64_t>(i) * g.ldc;
 #pragma unroll
     for (int mj = 0; mj < MJ; ++mj) {
@@ -353,7 +379,7 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs g, int batch_bas
           v[t] = acc[mj][ni][4 * q + t] + bv;
           if (g.relu) v[t] = fmaxf(v[t], 0.f);
         }
-        if (OUT_F32) {
+        if constexpr (OUT_F32 || sizeof(T) == 4) {
           float* c = reinterpret_cast<float*>(g.C) + row;
           if (vst && j + 4 <= g.N) {
             *reinterpret_cast<float4*>(c + col(j)) = make_float4(v[0], v[1], v[2], v[3]);
@@ -378,10 +404,10 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs g, int batch_bas
   }
 }
 
-template <int TJ, int TI, int WJ, bool OUT_F32>
+template <typename T, int TJ, int TI, int WJ, bool OUT_F32>
 hipError_t launch_dma_tile(const GemmArgs& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t stream) {
   using Sh = GemmDmaShape<TJ, TI, WJ>;
-  const auto kern = gemm_dma_kernel<TJ, TI, WJ, OUT_F32>;
+  const auto kern = gemm_dma_kernel<T, TJ, TI, WJ, OUT_F32>;
   const size_t lds = (size_t)Sh::NST * Sh::STAGE;
   static bool attr = false;
   if (!attr) {
@@ -390,39 +416,44 @@ hipError_t launch_dma_tile(const GemmArgs& g, uint32_t a_bytes, uint32_t b_bytes
     if (e != hipSuccess) return e;
     attr = true;
   }
-  for (int base = 0; base < g.batch; base += 65535) {
-    const int nb = g.batch - base < 65535 ? g.batch - base : 65535;
-    const dim3 grid((g.N + TJ - 1) / TJ, (g.M + TI - 1) / TI, nb);
-    hipLaunchKernelGGL(kern, grid, dim3(256), lds, stream, g, base, a_bytes, b_bytes);
-  }
+  const int njt = (g.N + TJ - 1) / TJ, nit = (g.M + TI - 1) / TI;
+  const int64_t units = (int64_t)njt * nit * g.batch;
+  if (units >= ((int64_t)1 << 30)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((units + 7) / 8 * 8)), dim3(256), lds, stream, g, njt, nit, a_bytes, b_bytes);
   return hipGetLastError();
 }
 
-// The DMA kernel serves bf16 operands whose rows are 16-byte aligned and
-// whose per-batch extents fit a buffer range.
-bool gemm_dma_ok(const GemmArgs& g, uint32_t& a_bytes, uint32_t& b_bytes) {
-  if (g.b_kmajor || g.Kred % 8 != 0 || g.lda % 8 != 0 || g.ldb % 8 != 0) return false;
-  if (g.sA0 % 8 != 0 || g.sA1 % 8 != 0 || g.sB0 % 8 != 0 || g.sB1 % 8 != 0) return false;
+// The DMA kernel serves operands whose rows are 16-byte aligned and whose
+// per-batch extents fit a buffer range.
+bool gemm_dma_ok(int dtype, const GemmArgs& g, uint32_t& a_bytes, uint32_t& b_bytes) {
+  const int es = dtype == DT_F32 ? 4 : 2, ue = 16 / es;
+  if (g.b_kmajor || g.Kred % ue != 0 || g.lda % ue != 0 || g.ldb % ue != 0) return false;
+  if (g.sA0 % ue != 0 || g.sA1 % ue != 0 || g.sB0 % ue != 0 || g.sB1 % ue != 0) return false;
   if (reinterpret_cast<uintptr_t>(g.A) % 16 != 0 || reinterpret_cast<uintptr_t>(g.B) % 16 != 0) return false;
   if (g.M <= 0 || g.N <= 0 || g.Kred <= 0) return false;
-  const int64_t ab = ((int64_t)(g.M - 1) * g.lda + g.Kred) * 2, bb = ((int64_t)(g.N - 1) * g.ldb + g.Kred) * 2;
+  const int64_t ab = ((int64_t)(g.M - 1) * g.lda + g.Kred) * es, bb = ((int64_t)(g.N - 1) * g.ldb + g.Kred) * es;
   if (ab >= ((int64_t)1 << 31) || bb >= ((int64_t)1 << 31)) return false;
   a_bytes = (uint32_t)ab;
   b_bytes = (uint32_t)bb;
   return true;
 }
 
-// Tile (TJ x TI) choice: the largest tile whose grid fills the CUs, with TI
-// no wider than M needs; small problems take the 64 x 64 tile.
-template <bool OUT_F32>
+// Tile (TJ x TI) choice.  fp32: 64 x 64, whose five workgroups per CU keep the
+// matrix units (a sixteenth of the bf16 rate) fed at any size (VGG block, two
+// layers: 313 us against 322 to 383 with the larger tiles).  bf16: the largest
+// tile whose grid fills the CUs, with TI no wider than M needs; small problems
+// take the 64 x 64 tile.
+template <typename T, bool OUT_F32>
 hipError_t launch_dma(const GemmArgs& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t stream) {
   auto wgs = [&](int tj, int ti) { return (int64_t)((g.N + tj - 1) / tj) * ((g.M + ti - 1) / ti) * g.batch; };
   const int mr = (g.M + 63) / 64 * 64;
-  if (mr >= 256 && wgs(128, 256) >= 240) return launch_dma_tile<128, 256, 1, OUT_F32>(g, a_bytes, b_bytes, stream);
-  if (mr >= 128 && wgs(128, 128) >= 240) return launch_dma_tile<128, 128, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
-  if (wgs(256, 64) >= 240) return launch_dma_tile<256, 64, 4, OUT_F32>(g, a_bytes, b_bytes, stream);
-  if (wgs(128, 64) >= 240) return launch_dma_tile<128, 64, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
-  return launch_dma_tile<64, 64, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
+  if constexpr (sizeof(T) == 2) {
+    if (mr >= 256 && wgs(128, 256) >= 240) return launch_dma_tile<T, 128, 256, 1, OUT_F32>(g, a_bytes, b_bytes, stream);
+    if (mr >= 128 && wgs(128, 128) >= 240) return launch_dma_tile<T, 128, 128, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
+    if (wgs(256, 64) >= 240) return launch_dma_tile<T, 256, 64, 4, OUT_F32>(g, a_bytes, b_bytes, stream);
+    if (wgs(128, 64) >= 240) return launch_dma_tile<T, 128, 64, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
+  }
+  return launch_dma_tile<T, 64, 64, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
 }
 
 template <typename T, int BM, int BN, bool OUT_F32, bool BKM>
@@ -458,9 +489,6 @@ hipError_t launch_typed(const GemmArgs& g, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_gemm_nt(int dtype, const GemmArgs& g, hipStream_t stream) {
-  if (dtype == DT_F32) {
-    return g.out_f32 ? launch_typed<float, true>(g, stream) : launch_typed<float, false>(g, stream);
-  }
   uint32_t ab = 0, bb = 0;
   // A batch that shares A and whose B items are consecutive rows is folded
   // into N when the items are narrow (IM2COL's small planes), so that the
@@ -474,7 +502,11 @@ hipError_t launch_gemm_nt(int dtype, const GemmArgs& g, hipStream_t stream) {
     f.batch = 1;
     f.sB0 = f.sC0 = 0;
   }
-  if (gemm_dma_ok(f, ab, bb)) return f.out_f32 ? launch_dma<true>(f, ab, bb, stream) : launch_dma<false>(f, ab, bb, stream);
+  if (gemm_dma_ok(dtype, f, ab, bb)) {
+    if (dtype == DT_F32) return launch_dma<float, true>(f, ab, bb, stream);
+    return f.out_f32 ? launch_dma<bf16_t, true>(f, ab, bb, stream) : launch_dma<bf16_t, false>(f, ab, bb, stream);
+  }
+  if (dtype == DT_F32) return launch_typed<float, true>(g, stream);
   return g.out_f32 ? launch_typed<bf16_t, true>(g, stream) : launch_typed<bf16_t, false>(g, stream);
 }
 

@@ -533,6 +533,36 @@ typedef short v8s_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) v4s_t lds_v4s_t;
 typedef __attribute__((address_space(3))) void lds_void_t;
 
+// LDS DMA for waves that also read the LDS themselves: copies 16 bytes per
+// lane from the buffer (offset voff per lane + soff) to lds + 16 * lane; lds
+// is the wave-uniform LDS byte address.  Offsets past the buffer copy zeros.
+// The builtin form makes the compiler wait for every outstanding DMA
+// (s_waitcnt vmcnt(0)) before any LDS read of the wave, which undoes a ring
+// of stages; written out, the transfer has no register result and the waits
+// are the caller's: CONVSEL_WAIT_VMCNT, then a barrier, before the data is
+// read.  (Operations that the compiler does not count can only make its own
+// vmcnt waits, for the loads it does count, wait longer.)  M0 is written
+// here; the compiler, which reserves it, sets it anew at each instruction of
+// its own that reads it, and a kernel uses one form of the DMA, not both.
+__device__ __forceinline__ u32x4_t dma_rsrc(const void* base, uint32_t bytes) {
+  const uint64_t p = reinterpret_cast<uint64_t>(base);
+  u32x4_t r;
+  r[0] = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(p)));
+  r[1] = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(p >> 32))) & 0xffffu;
+  r[2] = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bytes)));
+  r[3] = kRsrcWord3;
+  return r;
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)p));
+}
+__device__ __forceinline__ void dma16(const u32x4_t& rsrc, uint32_t lds, uint32_t voff, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory");
+}
+
 // Sum of the split partials, plus bias, ReLU, rounding to the output type;
 // kReducePer consecutive outputs per thread (flat index: outputs stay below
 // 2^31), read and written as vectors when all of them exist; the channel of

@@ -38,3 +38,43 @@ def test_im2col_tiles_are_bit_exact(case, dtype):
     col = cs.im2col(x.to(DEV), (R, S), st, pd, dl, G)
     torch.cuda.synchronize()
     assert np.array_equal(f64(col), oracle.im2col(f64(x), R, S, st, pd, dl, G))
+
+
+# Tile columns of the Winograd input transform: 7, 15 and 31 tiles per workgroup, one more and one less;
+# channel blocks of 32 with a remainder.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("tiles", [1, 6, 7, 8, 14, 15, 16, 28, 31, 32, 45])
+def test_winograd_input_transform_tiles(tiles, dtype):
+    for W, C, pad in ((2 * tiles, 33, 1), (2 * tiles + 1, 32, 0)):
+        if W + 2 * pad < 3:
+            continue
+        x = torch.randn(2, C, 5, W, generator=torch.Generator().manual_seed(W)).to(TDT[dtype])
+        say("winograd input tiles", tiles, W, C, pad, dtype)
+        V = cs.winograd_input_transform(x.to(DEV), padding=pad)
+        torch.cuda.synchronize()
+        ref = oracle.winograd_input_transform(f64(x), padding=pad).reshape(16, -1, C)
+        # three adds of fp32 values, then (bf16) one rounding, relative to the largest entry
+        tol = 4 * 2.0 ** -24 if dtype == "f32" else 2.0 ** -8
+        assert np.abs(f64(V) - ref).max() <= tol * np.abs(ref).max()
+
+
+# K, C, H, W of 1x1 IM2COL + GEMM layers: the products' tiles (64 or more rows and columns, k-tiles of 64 bf16 or
+# 32 fp32) with remainders on each axis, batches folded and not (planes of 1024 pixels), and reductions that are
+# no whole 16-byte units (the register-staged kernel).
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(64, 64, 8, 8), (65, 8, 7, 9), (63, 72, 9, 7), (130, 40, 32, 32), (8, 36, 33, 31),
+                                  (257, 200, 16, 17), (5, 7, 6, 6)], ids=str)
+def test_gemm_tiles(case, dtype):
+    K, C, H, W = case
+    g = torch.Generator().manual_seed(K)
+    x = torch.randn(3, C, H, W, generator=g).to(TDT[dtype])
+    w = torch.randn(K, C, 1, 1, generator=g).to(TDT[dtype])
+    b = torch.randn(K, generator=g).to(TDT[dtype])
+    say("gemm tiles", case, dtype)
+    y = cs.conv2d(x.to(DEV), w.to(DEV), b.to(DEV), algo="im2col_gemm", relu=True)
+    torch.cuda.synchronize()
+    ref = oracle.conv2d(f64(x), f64(w), f64(b), 1, 0, 1, 1, True)
+    # C + 1 fp32 roundings of sums whose terms' absolute values add up to S; bf16: one more of the result
+    S = oracle.conv2d(np.abs(f64(x)), np.abs(f64(w)), np.abs(f64(b)), 1, 0, 1, 1, False)
+    tol = (C + 1) * 2.0 ** -24 * S + (0 if dtype == "f32" else 2.0 ** -8 * np.abs(ref))
+    assert (np.abs(f64(y) - ref) <= tol + 1e-30).all()
