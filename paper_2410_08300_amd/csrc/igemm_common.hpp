@@ -557,6 +557,8 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)p));
 }
 __device__ __forceinline__ void dma16(const u32x4_t& rsrc, uint32_t lds, uint32_t voff, uint32_t soff) {
+  lds = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(lds)));
+  soff = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(soff)));
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
                : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)

@@ -113,6 +113,19 @@ hipError_t launch_implicit_gemm(const Shape& s, const void* x, const void* w, co
 std::string implicit_gemm_describe(const Shape& s);
 
 
+// Implicit GEMM on channels-last tensors (one group, any filter, stride and
+// dilation): x is N x H x W x Cp (Cp: C rounded up to 16 bytes, zeros past
+// C), the package [K][R*S][Cp]; y is N x P x Q x K (out_nhwc: K a multiple of
+// 16 bytes, y and res 16-byte aligned) or N x K x P x Q.  x and the package
+// are 16-byte aligned.  launch_to_nhwc writes such an x from N x C x HW.
+bool nhwc_applies(const Shape& s);
+size_t nhwc_packed_bytes(const Shape& s);
+size_t nhwc_input_bytes(const Shape& s);
+hipError_t nhwc_pack(const Shape& s, const void* w, void* pk, hipStream_t stream);
+hipError_t launch_to_nhwc(int dtype, const void* x, void* y, int64_t N, int64_t C, int64_t HW, hipStream_t stream);
+hipError_t nhwc_main(const Shape& s, const void* x, const void* pk, const void* b, void* y, const void* res,
+                     bool out_nhwc, hipStream_t stream);
+
 // Implicit precomputed-index GEMM: the package holds the zero-padded
 // filters and the reduction and pixel index tables; no other workspace.
 bool precomp_applies(const Shape& s);

@@ -14,9 +14,11 @@
 
 #include "../../include/convsel_model.h"
 #include "common.hpp"
+#include "kernels.hpp"
 
 using convsel::bf16_t;
 using convsel::elem;
+using convsel::vec16;
 
 namespace convsel {
 conv_status_t conv2d_prepacked_residual(const void* x, const void* packed, const void* b, const void* res, void* y,
@@ -106,6 +108,140 @@ __global__ __launch_bounds__(256) void global_avgpool_kernel(const T* __restrict
   if (lane == 0) elem<T>::store(y + plane, acc / static_cast<float>(HW));
 }
 
+// ---- the same on channels-last values (bf16, channels a multiple of 8) ------
+
+__device__ __forceinline__ float bf16_at(const vec16& v, int i) {
+  return __uint_as_float((i & 1) ? (v.d[i >> 1] & 0xffff0000u) : (v.d[i >> 1] << 16));
+}
+
+// One 16-byte unit (8 channels of one output pixel) per thread.
+template <bool MAX>
+__global__ __launch_bounds__(256) void pool_nhwc_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y, int H,
+                                                        int W, int P, int Q, int CU, int kh, int kw, int sh, int sw,
+                                                        int ph, int pw, int64_t units) {
+  const int64_t u = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (u >= units) return;
+  const int cu = static_cast<int>(u % CU);
+  const int64_t j = u / CU;
+  const int pq = static_cast<int>(j % (static_cast<int64_t>(P) * Q));
+  const int64_t n = j / (static_cast<int64_t>(P) * Q);
+  const int p = pq / Q, q = pq - p * Q;
+  const int ih0 = p * sh - ph, iw0 = q * sw - pw;
+  const bf16_t* xn = x + (n * H * W * CU + cu) * 8;
+  float acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = MAX ? -INFINITY : 0.f;
+  for (int r = 0; r < kh; ++r) {
+    const int ih = ih0 + r;
+    if (ih < 0 || ih >= H) continue;
+    for (int s = 0; s < kw; ++s) {
+      const int iw = iw0 + s;
+      if (iw < 0 || iw >= W) continue;
+      const vec16 v = convsel::load16(xn + (static_cast<int64_t>(ih) * W + iw) * CU * 8);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = MAX ? fmaxf(acc[i], bf16_at(v, i)) : acc[i] + bf16_at(v, i);
+    }
+  }
+  vec16 o;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const float k = static_cast<float>(kh * kw);
+    o.d[d] = MAX ? convsel::f32x2_to_bf16x2(acc[2 * d], acc[2 * d + 1])
+                 : convsel::f32x2_to_bf16x2(acc[2 * d] / k, acc[2 * d + 1] / k);
+  }
+  convsel::store16(y + u * 8, o);
+}
+
+// 3 x 3 pooling with stride 2 and padding 1 from N x C x H x W (W a multiple
+// of 8, x 16-byte aligned) into channels-last: the step after a stem.  A
+// workgroup takes 64 channels x 32 columns of one output row; a thread reads
+// the 17 input columns of 8 outputs with two 16-byte loads and one element per
+// row, and the tile is transposed in LDS.
+//
+// What bounds it: its bytes.  64 channels of 112 x 112, 32 images (51 MB read,
+// 13 MB written): 26 us; one output per thread with nine 2-byte loads each took
+// 32 us, and its result needed a transposition besides.
+template <bool MAX>
+__global__ __launch_bounds__(256) void pool3s2_to_nhwc_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y,
+                                                              int C, int H, int W, int P, int Q, int qtiles,
+                                                              int ctiles) {
+  __shared__ uint16_t tile[32 * 72];  // [column][channel], rows of 72 values
+  int b = blockIdx.x;
+  const int qt = b % qtiles;
+  b /= qtiles;
+  const int p = b % P;
+  b /= P;
+  const int ct = b % ctiles;
+  const int64_t n = b / ctiles;
+  const int c = threadIdx.x >> 2, g = threadIdx.x & 3;
+  const int q0 = qt * 32 + g * 8, iw = 2 * q0;
+  float acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = MAX ? -INFINITY : 0.f;
+  const bool on = ct * 64 + c < C && iw < W;
+  const bf16_t* xp = x + (n * C + (on ? ct * 64 + c : 0)) * static_cast<int64_t>(H) * W;
+  vec16 lo[3], hi[3];
+  float left[3];
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    const int ih = 2 * p - 1 + r;
+    const bool in = on && ih >= 0 && ih < H;
+    const bf16_t* row = xp + (in ? static_cast<int64_t>(ih) * W : 0);
+    const bool in_hi = in && iw + 8 < W, in_left = in && iw > 0;
+    lo[r] = convsel::load16(row + (in ? iw : 0));
+    hi[r] = convsel::load16(row + (in_hi ? iw + 8 : 0));
+    left[r] = elem<bf16_t>::load(row + (in_left ? iw - 1 : 0));
+    const uint32_t pad = MAX ? 0xff80ff80u : 0u;  // -infinity, or 0
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      lo[r].d[d] = in ? lo[r].d[d] : pad;
+      hi[r].d[d] = in_hi ? hi[r].d[d] : pad;
+    }
+    if (!in_left) left[r] = MAX ? -INFINITY : 0.f;
+  }
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    auto at = [&](int i) { return i < 0 ? left[r] : i < 8 ? bf16_at(lo[r], i) : bf16_at(hi[r], i - 8); };
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int s = 0; s < 3; ++s) acc[i] = MAX ? fmaxf(acc[i], at(2 * i - 1 + s)) : acc[i] + at(2 * i - 1 + s);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) tile[(g * 8 + i) * 72 + c] = convsel::f32_to_bf16(MAX ? acc[i] : acc[i] / 9.f);
+  __syncthreads();
+  const int q = threadIdx.x >> 3, cu = threadIdx.x & 7;
+  const int qo = qt * 32 + q;
+  if (qo >= Q || ct * 64 + cu * 8 >= C) return;
+  const vec16 v = convsel::load16(tile + q * 72 + cu * 8);
+  convsel::store16(y + ((n * P + p) * Q + qo) * C + ct * 64 + cu * 8, v);
+}
+
+// Global average of N x HW x C: a workgroup takes 64 channels of one image,
+// 32 threads per 8 channels, summed through LDS in a fixed order.
+__global__ __launch_bounds__(256) void global_avgpool_nhwc_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y,
+                                                                  int HW, int CU, int ctiles) {
+  __shared__ float part[32][65];
+  const int ct = blockIdx.x % ctiles;
+  const int64_t n = blockIdx.x / ctiles;
+  const int cl = threadIdx.x & 7, pl = threadIdx.x >> 3, cu = ct * 8 + cl;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (cu < CU)
+    for (int i = pl; i < HW; i += 32) {
+      const vec16 v = convsel::load16(x + ((n * HW + i) * CU + cu) * 8);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc[k] += bf16_at(v, k);
+    }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) part[pl][cl * 8 + k] = acc[k];
+  __syncthreads();
+  const int c = threadIdx.x;
+  if (c >= 64 || ct * 64 + c >= CU * 8) return;
+  float s = 0.f;
+  for (int i = 0; i < 32; ++i) s += part[i][c];
+  elem<bf16_t>::store(y + n * CU * 8 + ct * 64 + c, s / static_cast<float>(HW));
+}
+
 unsigned blocks_for(int64_t n, int per = 256) { return static_cast<unsigned>((n + per - 1) / per); }
 
 // ---- model ----------------------------------------------------------------
@@ -120,6 +256,12 @@ struct Value {
   int falias = -1;    // planned: a fused add's output shares its convolution's storage
   int64_t offset = -1;
   int64_t bytes = 0;
+  // planned: held channels-last (bf16 images between the convolutions of the
+  // channels-last path), and the place of a channels-last copy of a value that
+  // is not (-1: none), written just before its first reader cl_first
+  bool cl = false;
+  int64_t cl_offset = -1;
+  int cl_first = -1, cl_last = -1;
   int64_t elems() const {
     int64_t e = 1;
     for (int i = 0; i < ndim; ++i) e *= d[i];
@@ -144,6 +286,8 @@ struct Op {
   int res = -1;
   int relu_eff = 0;
   bool skip = false;
+  bool cl = false;  // planned: a convolution that runs the channels-last kernel
+  convsel::Shape shape{};
   conv2d_desc_t desc{};
   int64_t pk_off = -1, pk_bytes = 0, bias_off = -1, ws_bytes = 0;
   // pooling
@@ -231,6 +375,193 @@ hipError_t launch_elementwise(const Op& op, const void* a, const void* b, void* 
       return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+// Pooling and global average pooling with a channels-last value on either side.
+hipError_t launch_channels_last(const Op& op, const void* a, void* y, const Value& vin, const Value& vout, bool in_cl,
+                                hipStream_t st) {
+  const bf16_t* x = reinterpret_cast<const bf16_t*>(a);
+  bf16_t* o = reinterpret_cast<bf16_t*>(y);
+  const int C = (int)vin.d[1], H = (int)vin.d[2], W = (int)vin.d[3];
+  if (op.kind == OP_GAP) {
+    const int ctiles = (C + 63) / 64;
+    hipLaunchKernelGGL(global_avgpool_nhwc_kernel, dim3((unsigned)(vin.d[0] * ctiles)), dim3(256), 0, st, x, o, H * W,
+                       C / 8, ctiles);
+    return hipGetLastError();
+  }
+  const int P = (int)vout.d[2], Q = (int)vout.d[3];
+  if (in_cl) {
+    const int64_t units = vout.elems() / 8;
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(blocks_for(units)), dim3(256), 0, st, x, o, H, W, P, Q, C / 8, op.kh, op.kw, op.sh,
+                         op.sw, op.ph, op.pw, units);
+    };
+    if (op.pool_kind == 0) go(pool_nhwc_kernel<true>);
+    else go(pool_nhwc_kernel<false>);
+    return hipGetLastError();
+  }
+  const int qtiles = (Q + 31) / 32, ctiles = (C + 63) / 64;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)(vin.d[0] * ctiles * P * qtiles)), dim3(256), 0, st, x, o, C, H, W, P, Q,
+                       qtiles, ctiles);
+  };
+  if (op.pool_kind == 0) go(pool3s2_to_nhwc_kernel<true>);
+  else go(pool3s2_to_nhwc_kernel<false>);
+  return hipGetLastError();
+}
+
+// A convolution of the channels-last path (operation number `index`): its
+// input's copy first, when this is the first operation that reads one.
+conv_status_t run_channels_last(const convsel_model& m, const Op& op, const void* x, const void* res, void* y,
+                                int index, hipStream_t st) {
+  const Value& in = m.vals[m.root(op.in)];
+  if (in.cl_offset >= 0) {
+    char* copy = m.arena + in.cl_offset;
+    if (in.cl_first == index) {
+      const conv_status_t s =
+          from_hip(convsel::launch_to_nhwc(convsel::DT_BF16, x, copy, op.shape.N, op.shape.C, op.shape.H * op.shape.W, st));
+      if (s != CONV_OK) return s;
+    }
+    x = copy;
+  }
+  convsel::Shape s = op.shape;
+  s.relu = op.relu_eff != 0;
+  return from_hip(convsel::nhwc_main(s, x, m.arena + op.pk_off, op.b ? m.arena + op.bias_off : nullptr, y, res,
+                                     m.vals[m.root(op.out)].cl, st));
+}
+
+// Channels-last planning (bf16).  An implicit GEMM convolution (one group, C
+// and K multiples of 8) can run the channels-last kernel, which needs no
+// transposition of its input; a value between two such operations is then held
+// as N x H x W x C.  A value qualifies when everything that writes or reads it
+// can handle that: those convolutions, pooling, global average pooling, and
+// adds and ReLUs whose values all qualify; flattens only of 1 x 1 planes,
+// where the two layouts are the same.  The model's input and output stay N x C
+// x H x W; a convolution on either end reads a channels-last copy of its input
+// (one copy per value, made by a transposing pass) or writes N x K x P x Q
+// itself.  A convolution with no such neighbour keeps the kernels of its own:
+// the transposing pass alone would cost more than it gains.
+void plan_layouts(convsel_model& m, int out_root) {
+  const int nv = (int)m.vals.size();
+  for (Value& v : m.vals) {
+    v.cl = false;
+    v.cl_offset = -1;
+    v.cl_first = v.cl_last = -1;
+  }
+  for (Op& op : m.ops) op.cl = false;
+  if (m.dtype != CONV_BF16) return;
+  std::vector<char> can(m.ops.size(), 0);  // convolutions the kernel serves
+  auto plane1 = [&](int v) { return m.vals[v].ndim == 2 || m.vals[v].d[2] * m.vals[v].d[3] == 1; };
+  for (size_t i = 0; i < m.ops.size(); ++i) {
+    Op& op = m.ops[i];
+    if (op.kind != OP_CONV) continue;
+    const conv2d_desc_t& d = op.desc;
+    int64_t P = 0, Q = 0;
+    conv2d_output_shape(&d, &P, &Q);
+    convsel::Shape& s = op.shape;
+    s.N = d.n; s.C = d.c; s.H = d.h; s.W = d.w; s.K = d.k; s.R = d.r; s.S = d.s; s.P = P; s.Q = Q;
+    s.G = d.groups; s.Cg = d.c / d.groups; s.Kg = d.k / d.groups;
+    s.sh = d.stride_h; s.sw = d.stride_w; s.ph = d.pad_h; s.pw = d.pad_w; s.dh = d.dil_h; s.dw = d.dil_w;
+    s.dtype = convsel::DT_BF16;
+    s.bias = d.has_bias != 0;
+    s.relu = d.fuse_relu != 0;
+    can[i] = op.algo_run == CONV_ALGO_IMPLICIT_GEMM && s.C % 8 == 0 && s.K % 8 == 0 && convsel::nhwc_applies(s);
+  }
+  // Candidates: storage roots, then those with an operation that cannot are
+  // struck out until nothing changes.
+  std::vector<char> cl(nv, 0);
+  for (int v = 1; v < nv; ++v)
+    cl[v] = m.vals[v].alias < 0 && m.vals[v].falias < 0 && v != out_root && m.vals[v].ndim == 4 &&
+            m.vals[v].d[1] % 8 == 0 && !plane1(v);
+  for (bool changed = true; changed;) {
+    changed = false;
+    auto strike = [&](int v) {
+      if (cl[v]) {
+        cl[v] = 0;
+        changed = true;
+      }
+    };
+    auto same = [&](int a, int b) {  // both channels-last or neither
+      if (cl[a] != cl[b]) {
+        strike(a);
+        strike(b);
+      }
+    };
+    for (size_t i = 0; i < m.ops.size(); ++i) {
+      const Op& op = m.ops[i];
+      const int in = m.root(op.in), out = m.root(op.out);
+      switch (op.kind) {
+        case OP_CONV:
+          if (!can[i]) {
+            strike(in);
+            strike(out);
+          }
+          if (op.res >= 0) same(m.root(op.res), out);
+          break;
+        case OP_POOL: {
+          const bool from_nchw = op.kh == 3 && op.kw == 3 && op.sh == 2 && op.sw == 2 && op.ph == 1 && op.pw == 1 &&
+                                 m.vals[op.in].d[3] % 8 == 0 && in != 0;  // (pool3s2_to_nhwc_kernel)
+          if (cl[in] && !cl[out] && !plane1(op.out)) strike(in);
+          if (cl[out] && !cl[in] && !from_nchw) strike(out);
+          break;
+        }
+        case OP_GAP:
+          break;
+        case OP_ADD:
+          if (op.skip) break;
+          same(m.root(op.in2), out);
+          same(in, out);
+          break;
+        case OP_RELU:
+          same(in, out);
+          break;
+        case OP_FLATTEN:
+          if (!plane1(op.in)) strike(in);
+          break;
+      }
+    }
+  }
+  // Copies have to pay.  On planes of whole 16-byte rows the N x C x H x W
+  // kernels are as fast (28 x 28 bottleneck, 32 images: 46 us, channels-last 62,
+  // of which the copy of its input 12), on others they repack planes or read
+  // pixel pairs and take up to twice the time.  So a network whose input needs
+  // a copy goes channels-last only with such planes in it, or when the copy is
+  // small (2 MB: 3 us, where the many launches of a small batch matter more).
+  int64_t copied = 0;
+  bool odd = false;
+  for (size_t i = 0; i < m.ops.size(); ++i) {
+    const Op& op = m.ops[i];
+    if (op.kind != OP_CONV || !can[i]) continue;
+    const int in = m.root(op.in), out = m.root(op.out);
+    if (!cl[in] && !cl[out]) continue;
+    if (!cl[in] && !plane1(op.in)) copied += m.vals[in].elems() * 2;
+    odd = odd || op.shape.P * op.shape.Q % 8 != 0 || (op.shape.H * op.shape.W % 8 != 0 && op.shape.R == 1);
+  }
+  if (copied > (2 << 20) && !odd) return;
+  for (int v = 0; v < nv; ++v) m.vals[v].cl = cl[v];
+  for (size_t i = 0; i < m.ops.size(); ++i) {
+    Op& op = m.ops[i];
+    if (op.kind != OP_CONV || !can[i]) continue;
+    const int in = m.root(op.in), out = m.root(op.out);
+    if (!cl[in] && !cl[out] && !(plane1(op.in) && in != 0 && op.shape.P * op.shape.Q == 1)) continue;
+    op.cl = true;
+    if (!cl[in] && (!plane1(op.in) || in == 0)) {  // (the caller's tensor may not be 16-byte aligned)
+      Value& v = m.vals[in];
+      if (v.cl_first < 0) v.cl_first = (int)i;
+      v.cl_last = (int)i;
+    }
+  }
+  // A convolution between values that both stay as they are uses a copy that
+  // exists anyway (the projection of a residual block beside its first layer).
+  for (size_t i = 0; i < m.ops.size(); ++i) {
+    Op& op = m.ops[i];
+    if (op.kind != OP_CONV || !can[i] || op.cl) continue;
+    Value& v = m.vals[m.root(op.in)];
+    if (v.cl_first < 0) continue;
+    op.cl = true;
+    v.cl_first = std::min(v.cl_first, (int)i);
+    v.cl_last = std::max(v.cl_last, (int)i);
+  }
 }
 
 }  // namespace
@@ -353,9 +684,7 @@ conv_status_t convsel_model_plan(convsel_model_t* model, int64_t n, int64_t c, i
   Value& in = m.vals[0];
   in.ndim = 4;
   in.d[0] = n; in.d[1] = c; in.d[2] = h; in.d[3] = w;
-  // Shapes, algorithms, packages and workspaces, in operation order.
-  int64_t off = 0;
-  m.ws_bytes = 0;
+  // Shapes and algorithms, in operation order.
   for (Op& op : m.ops) {
     const Value& a = m.vals[op.in];
     Value& o = m.vals[op.out];
@@ -376,19 +705,6 @@ conv_status_t convsel_model_plan(convsel_model_t* model, int64_t n, int64_t c, i
         const conv_status_t st = conv2d_check(&d, al);
         if (st != CONV_OK) return st;
         op.algo_run = al;
-        size_t pk = 0, ws = 0;
-        if (conv2d_packed_filter_bytes(&d, al, &pk) != CONV_OK || conv2d_prepacked_workspace_bytes(&d, al, &ws) != CONV_OK)
-          return CONV_ERR_INVALID_ARG;
-        op.pk_off = off;
-        op.pk_bytes = (int64_t)pk;
-        off = align_up(off + (int64_t)pk);
-        op.bias_off = -1;
-        if (op.b) {
-          op.bias_off = off;
-          off = align_up(off + op.k * es);
-        }
-        op.ws_bytes = (int64_t)ws;
-        m.ws_bytes = std::max(m.ws_bytes, (int64_t)ws);
         if (op.linear) {
           o.ndim = 2;
           o.d[0] = a.d[0]; o.d[1] = op.k; o.d[2] = o.d[3] = 0;
@@ -476,6 +792,29 @@ conv_status_t convsel_model_plan(convsel_model_t* model, int64_t n, int64_t c, i
   // The output must come out of an operation, not be the input itself.
   const int out_root = m.root(m.output);
   if (out_root == 0) return CONV_ERR_UNSUPPORTED;
+  plan_layouts(m, out_root);
+  // Filter packages, biases and the largest workspace.
+  int64_t off = 0;
+  m.ws_bytes = 0;
+  for (Op& op : m.ops) {
+    if (op.kind != OP_CONV) continue;
+    size_t pk = 0, ws = 0;
+    if (op.cl)
+      pk = convsel::nhwc_packed_bytes(op.shape);
+    else if (conv2d_packed_filter_bytes(&op.desc, op.algo_run, &pk) != CONV_OK ||
+             conv2d_prepacked_workspace_bytes(&op.desc, op.algo_run, &ws) != CONV_OK)
+      return CONV_ERR_INVALID_ARG;
+    op.pk_off = off;
+    op.pk_bytes = (int64_t)pk;
+    off = align_up(off + (int64_t)pk);
+    op.bias_off = -1;
+    if (op.b) {
+      op.bias_off = off;
+      off = align_up(off + op.k * es);
+    }
+    op.ws_bytes = (int64_t)ws;
+    m.ws_bytes = std::max(m.ws_bytes, (int64_t)ws);
+  }
   // Lifetimes of the storage roots: [producer, last reader].
   const int nv = (int)m.vals.size();
   std::vector<int> last(nv, -1), first(nv, -1);
@@ -492,30 +831,39 @@ conv_status_t convsel_model_plan(convsel_model_t* model, int64_t n, int64_t c, i
   m.ws_off = off;
   off = align_up(off + m.ws_bytes);
   const int64_t act_base = off;
-  std::vector<int> order;
-  for (int i = 1; i < nv; ++i)
-    if (m.vals[i].alias < 0 && m.vals[i].falias < 0 && i != out_root) order.push_back(i);
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return m.vals[a].bytes > m.vals[b].bytes; });
+  // Blocks to place: the storage roots and the channels-last copies.
+  struct Block {
+    int64_t need, offset;
+    int first, last, value;
+    bool copy;
+  };
+  std::vector<Block> order;
+  for (int i = 0; i < nv; ++i) {
+    const Value& v = m.vals[i];
+    if (i > 0 && v.alias < 0 && v.falias < 0 && i != out_root)
+      order.push_back({align_up(v.bytes), 0, first[i], last[i], i, false});
+    if (v.cl_first >= 0) order.push_back({align_up(v.elems() * es), 0, v.cl_first, v.cl_last, i, true});
+  }
+  std::stable_sort(order.begin(), order.end(), [&](const Block& x, const Block& y) { return x.need > y.need; });
   std::vector<int> placed;
   int64_t act_top = 0;
-  for (int v : order) {
-    // Intervals [offset, offset + bytes) of placed values live at the same time, sorted by offset.
+  for (int v = 0; v < (int)order.size(); ++v) {
+    // Intervals [offset, offset + bytes) of placed blocks live at the same time, sorted by offset.
     std::vector<std::pair<int64_t, int64_t>> busy;
     for (int u : placed)
-      if (first[u] <= last[v] && first[v] <= last[u])
-        busy.push_back({m.vals[u].offset, m.vals[u].offset + align_up(m.vals[u].bytes)});
+      if (order[u].first <= order[v].last && order[v].first <= order[u].last)
+        busy.push_back({order[u].offset, order[u].offset + order[u].need});
     std::sort(busy.begin(), busy.end());
     int64_t cand = 0;
-    const int64_t need = align_up(m.vals[v].bytes);
     for (const auto& iv : busy) {
-      if (cand + need <= iv.first) break;
+      if (cand + order[v].need <= iv.first) break;
       cand = std::max(cand, iv.second);
     }
-    m.vals[v].offset = cand;
-    act_top = std::max(act_top, cand + need);
+    order[v].offset = cand;
+    act_top = std::max(act_top, cand + order[v].need);
     placed.push_back(v);
   }
-  for (int v : order) m.vals[v].offset += act_base;
+  for (const Block& bl : order) (bl.copy ? m.vals[bl.value].cl_offset : m.vals[bl.value].offset) = bl.offset + act_base;
   m.arena_bytes = act_base + act_top;
   *arena_bytes = (size_t)m.arena_bytes;
   m.planned = true;
@@ -551,7 +899,8 @@ conv_status_t convsel_model_bind(convsel_model_t* model, void* arena, size_t are
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   for (Op& op : m.ops) {
     if (op.kind != OP_CONV) continue;
-    conv_status_t s = conv2d_pack_filters(op.w, base + op.pk_off, &op.desc, op.algo_run, stream);
+    conv_status_t s = op.cl ? from_hip(convsel::nhwc_pack(op.shape, op.w, base + op.pk_off, st))
+                            : conv2d_pack_filters(op.w, base + op.pk_off, &op.desc, op.algo_run, stream);
     if (s != CONV_OK) return s;
     if (op.b) {
       s = from_hip(hipMemcpyAsync(base + op.bias_off, op.b, (size_t)(op.k * m.esize()), hipMemcpyDeviceToDevice, st));
@@ -574,13 +923,18 @@ conv_status_t convsel_model_forward(convsel_model_t* model, const void* x, void*
     if (r == out_root) return reinterpret_cast<char*>(y);
     return m.arena + m.vals[r].offset;
   };
-  for (const Op& op : m.ops) {
+  for (int i = 0; i < (int)m.ops.size(); ++i) {
+    const Op& op = m.ops[i];
     const Value& vin = m.vals[op.in];
     const Value& vout = m.vals[op.out];
     conv_status_t s = CONV_OK;
     if (op.skip) continue;  // an add fused into its convolution
     switch (op.kind) {
       case OP_CONV:
+        if (op.cl) {
+          s = run_channels_last(m, op, ptr(op.in), op.res >= 0 ? ptr(op.res) : nullptr, ptr(op.out), i, st);
+          break;
+        }
         if (op.res >= 0)
           s = convsel::conv2d_prepacked_residual(
               ptr(op.in), m.arena + op.pk_off, op.b ? m.arena + op.bias_off : nullptr, ptr(op.res), ptr(op.out),
@@ -592,6 +946,13 @@ conv_status_t convsel_model_forward(convsel_model_t* model, const void* x, void*
         break;
       case OP_FLATTEN:
         break;
+      case OP_POOL:
+      case OP_GAP:
+        if (m.vals[m.root(op.in)].cl || m.vals[m.root(op.out)].cl) {
+          s = from_hip(launch_channels_last(op, ptr(op.in), ptr(op.out), vin, vout, m.vals[m.root(op.in)].cl, st));
+          break;
+        }
+        [[fallthrough]];
       default:
         s = from_hip(m.dtype == CONV_F32
                          ? launch_elementwise<float>(op, ptr(op.in), op.in2 >= 0 ? ptr(op.in2) : nullptr,
@@ -619,6 +980,11 @@ conv_status_t convsel_model_describe(const convsel_model_t* model, char* buf, si
              (long long)o.d[0], (long long)o.d[1], (long long)o.d[2], (long long)o.d[3]);
     d += line;
     if (op.kind == OP_CONV) d += std::string(" algo=") + conv2d_algo_name(model->planned ? op.algo_run : op.algo);
+    if (model->planned && op.cl) {
+      d += " channels_last";
+      const Value& in = model->vals[model->root(op.in)];
+      if (in.cl_offset >= 0) d += " copy@" + std::to_string(in.cl_offset);
+    }
     if (model->planned && op.res >= 0) d += " + v" + std::to_string(op.res);
     if (model->planned ? (op.kind == OP_CONV ? op.relu_eff : op.relu) : op.relu) d += " relu";
     if (model->planned && op.skip) d += " fused";

@@ -221,3 +221,28 @@ def test_residual_fusion_only_where_it_is_exact():
     assert " + v1" in conv_b and any(line.split()[1] == "add" and " fused" in line for line in d)
     d = _lowered(Plain(), shape)
     assert d[0].startswith("0 conv v0 -> v1") and " + v0 relu " in d[0] + " " and d[1].endswith("fused offset=-1")
+
+
+def test_channels_last_plan():
+    """bf16 implicit GEMM chains are planned channels-last; the copy of the
+    model's input that the first convolution then reads lies inside the
+    arena, apart from every value and package that is live with it."""
+    net = nn.Sequential(nn.Conv2d(64, 16, 1), nn.ReLU(), nn.Conv2d(16, 16, 3, 1, 1), nn.ReLU(),
+                        nn.Conv2d(16, 64, 1)).to(torch.bfloat16)
+    m = cs.swap_backend(net, "implicit_gemm")
+    nbytes = m._native.plan(8, 64, 28, 28)
+    d = m._native.describe().splitlines()
+    assert sum("channels_last" in line for line in d) == 3
+    copy = int(d[0].split("copy@")[1].split()[0])
+    size = 8 * 64 * 28 * 28 * 2
+    ws = int(d[-1].split("@")[1])
+    assert copy >= ws and copy + size <= nbytes
+    off, nb = m._native.placement(1)               # conv1's output: written while the copy is read
+    assert off + nb <= copy or copy + size <= off
+    # a lone convolution keeps its own kernels, and so does a float32 model
+    lone = cs.swap_backend(nn.Sequential(nn.Conv2d(64, 16, 3)).to(torch.bfloat16), "implicit_gemm")
+    lone._native.plan(2, 64, 14, 14)
+    assert "channels_last" not in lone._native.describe()
+    f32 = cs.swap_backend(nn.Sequential(nn.Conv2d(64, 16, 1), nn.Conv2d(16, 64, 1)), "implicit_gemm")
+    f32._native.plan(2, 64, 14, 14)
+    assert "channels_last" not in f32._native.describe()

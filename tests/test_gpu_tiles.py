@@ -78,3 +78,98 @@ def test_gemm_tiles(case, dtype):
     S = oracle.conv2d(np.abs(f64(x)), np.abs(f64(w)), np.abs(f64(b)), 1, 0, 1, 1, False)
     tol = (C + 1) * 2.0 ** -24 * S + (0 if dtype == "f32" else 2.0 ** -8 * np.abs(ref))
     assert (np.abs(f64(y) - ref) <= tol + 1e-30).all()
+
+
+class Chain(torch.nn.Module):
+    """Two or three convolutions that run channels-last: R x S with stride, padding and dilation, 1 x 1, and
+    (with a residual) 3 x 3 back to the first one's channels."""
+
+    def __init__(self, c, k, r, st, pad, dil, k2, res):
+        super().__init__()
+        self.a = torch.nn.Conv2d(c, k, r, st, pad, dil)
+        self.b = torch.nn.Conv2d(k, k2, 1)
+        self.c = torch.nn.Conv2d(k2, k, 3, 1, 1)
+        self.res = res
+
+    def forward(self, x):
+        y = torch.relu(self.a(x))
+        z = self.c(torch.relu(self.b(y)))
+        return torch.relu(z + y) if self.res else z
+
+
+# N, C, H, W, K, R, stride, pad, dilation, K2, residual.  Together the plans reach every tile (128 x 128 to 32 x 32,
+# two to eight stages, one and four wave groups), both tap modes (C whole 128-byte pieces or not), and output rows of
+# 8, 4 and single pixels; 4 bytes' worth of copy and a plane of odd size each make the chain channels-last.
+CHAINS = [
+    (1, 64, 14, 14, 64, 3, 1, 1, 1, 128, True),
+    (3, 72, 15, 16, 40, 3, 2, 1, 1, 64, True),
+    (1, 8, 9, 10, 16, 5, 1, 2, 1, 8, False),
+    (2, 24, 17, 18, 72, 7, 2, 3, 1, 40, True),
+    (1, 64, 20, 20, 64, 3, 1, 2, 2, 64, True),
+    (5, 16, 7, 8, 200, 1, 1, 0, 1, 136, True),
+    (1, 512, 7, 7, 512, 3, 1, 1, 1, 64, False),
+    (4, 128, 16, 16, 256, 3, 1, 1, 1, 64, True),
+    (40, 64, 14, 14, 256, 1, 1, 0, 1, 64, True),
+    (150, 128, 14, 14, 64, 3, 1, 1, 1, 128, False),
+    (64, 64, 27, 27, 128, 1, 2, 0, 1, 256, True),
+    (16, 8, 45, 45, 64, 3, 1, 1, 1, 512, False),
+]
+
+
+@pytest.mark.parametrize("case", CHAINS, ids=str)
+def test_channels_last_chain(case):
+    N, C, H, W, K, R, st, pad, dil, K2, res = case
+    torch.manual_seed(C + K)
+    net = Chain(C, K, R, st, pad, dil, K2, res).to(torch.bfloat16).eval()
+    x = torch.randn(N, C, H, W).to(torch.bfloat16)
+    model = cs.swap_backend(net.to(DEV), "implicit_gemm")
+    say("channels-last chain", case)
+    y = model(x.to(DEV))
+    torch.cuda.synchronize()
+    assert model.describe().count("channels_last") >= 2
+    again = model(x.to(DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(y, again)
+
+    def conv(v, m, relu):
+        o = oracle.conv2d(v, f64(m.weight), f64(m.bias), m.stride[0], m.padding[0], m.dilation[0], 1, relu)
+        return torch.from_numpy(o).to(torch.bfloat16).double().numpy()  # stored values are bf16
+
+    a = conv(f64(x), net.a, True)
+    z = conv(conv(a, net.b, True), net.c, False)
+    ref = np.maximum(z + a, 0) if res else z
+    # three bf16 roundings of fp32 sums on each side, the first two spread over sums of the later layers
+    assert np.abs(f64(y) - ref).max() <= 3 * 2.0 ** -8 * np.abs(ref).max()
+
+
+class Stem(torch.nn.Module):
+    def __init__(self, kind, k, c=64):
+        super().__init__()
+        self.a = torch.nn.Conv2d(3, c, 3, 1, 1)
+        self.pool = (torch.nn.MaxPool2d if kind == "max" else torch.nn.AvgPool2d)(*k)
+        self.b = torch.nn.Conv2d(c, 64, 1)
+        self.c = torch.nn.Conv2d(64, 16, 1)
+        self.gap = torch.nn.AdaptiveAvgPool2d(1)
+
+    def forward(self, x):
+        return torch.flatten(self.gap(self.c(self.b(self.pool(self.a(x))))), 1)
+
+
+@pytest.mark.parametrize("kind", ["max", "avg"])
+@pytest.mark.parametrize("c", [64, 72])
+@pytest.mark.parametrize("hw,k", [((16, 24), (3, 2, 1)), ((13, 72), (3, 2, 1)), ((15, 136), (3, 2, 1)),
+                                  ((14, 14), (2, 2, 0))], ids=str)
+def test_channels_last_pooling(kind, c, hw, k):
+    """Pooling into channels-last (3 x 3, stride 2: 16 input columns per thread, 32 output columns per tile, 64
+    channels per tile), and global average pooling out of it, against the same network in float64."""
+    torch.manual_seed(hw[1])
+    net = Stem(kind, k, c).to(torch.bfloat16).eval()
+    x = torch.randn(2, 3, *hw).to(torch.bfloat16)
+    say("channels-last pooling", kind, c, hw, k)
+    model = cs.swap_backend(net.to(DEV), "implicit_gemm")
+    y = model(x.to(DEV))
+    torch.cuda.synchronize()
+    assert "channels_last" in model.describe()
+    ref = net.cpu().double()(x.double()).detach().numpy()
+    # five bf16 roundings, averaged over the plane
+    assert np.abs(f64(y) - ref).max() <= 5 * 2.0 ** -8 * np.abs(ref).max()
