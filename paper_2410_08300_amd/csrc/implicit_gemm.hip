@@ -1789,6 +1789,33 @@ std::string describe_typed(const Shape& s) {
 
 }  // namespace
 
+namespace {
+// bf16 layers that go to the channels-last kernel (a transposing copy of the
+// input, then the DMA kernel), measured prepacked against the kernel each would
+// take otherwise, 90 random layers:
+//  * instead of implicit_gemm_kernel (5 x 5, 7 x 7, dilated or strided 3 x 3
+//    filters): 0.93 to 3.7 times as fast, median 1.5 (5 x 5, stride 2, 256 ->
+//    256 of 28 x 28, 128 images: 211 -> 135 us); not for strided 3 x 3 filters
+//    with at most 8 channels, 0.67 to 0.94, whose copy pads channels and holds
+//    four times the pixels that are read;
+//  * instead of implicit_ws_kernel (3 x 3): 1.1 to 1.5 with fewer than 64
+//    channels, of which that kernel's chunks pad most, and for small layers
+//    below 128 channels, which it splits and reduces; 0.6 to 0.9 with more,
+//    where its own channel split fills the chip better.
+// Below 4 MFLOP both are a few launches and nothing else.
+bool use_nhwc(const Shape& s) {
+  if (s.dtype != DT_BF16 || use_pointwise(s) || rows_applies(s) || k3_applies(s)) return false;
+  const double macs = (double)s.N * s.P * s.Q * s.K * s.C * s.R * s.S;
+  if (macs < 2e6) return false;
+  if (ws_applies(s)) {
+    if (!(s.C < 64 || (s.C < 128 && (double)s.N * s.P * s.Q * s.K < 64.0 * 128 * 128))) return false;
+  } else if (s.R * s.S <= 9 && (s.sh > 1 || s.sw > 1) && s.C <= 8) {
+    return false;
+  }
+  return nhwc_layer_applies(s);
+}
+}  // namespace
+
 bool implicit_gemm_fits(const Shape& s) {
   if (use_pointwise(s) || rows_applies(s) || k3_applies(s) || ws_applies(s)) return true;
   IgPlan pl;
@@ -1800,6 +1827,7 @@ size_t implicit_gemm_packed_bytes(const Shape& s) {
   if (use_pointwise(s)) return (size_t)(s.K * s.C * s.esize());  // a plain copy of the filters
   if (rows_applies(s)) return rows_packed_bytes(s);
   if (k3_applies(s)) return k3_uses_package(s) ? k3_package_bytes(s) : (size_t)(s.K * s.C * 9 * 2);
+  if (use_nhwc(s)) return nhwc_layer_packed_bytes(s);
   if (ws_applies(s)) return ws_packed_bytes(s);
   IgPlan pl;
   const bool ok = s.dtype == DT_F32 ? make_plan<float>(s, pl) : make_plan<bf16_t>(s, pl);
@@ -1809,6 +1837,7 @@ size_t implicit_gemm_packed_bytes(const Shape& s) {
 size_t implicit_gemm_split_bytes(const Shape& s) {
   if (rows_applies(s)) return 0;
   if (k3_applies(s)) return k3_split_bytes(s);
+  if (use_nhwc(s)) return nhwc_layer_bytes(s);
   if (ws_applies(s)) return ws_split_bytes(s);
   if (use_pointwise(s)) return s.dtype == DT_F32 ? pw_split_bytes<float>(s) : pw_split_bytes<bf16_t>(s);
   return s.dtype == DT_F32 ? split_bytes_typed<float>(s) : split_bytes_typed<bf16_t>(s);
@@ -1822,6 +1851,7 @@ hipError_t launch_implicit_pack(const Shape& s, const void* w, void* wp, hipStre
   if (rows_applies(s)) return rows_pack(s, w, wp, stream);
   if (k3_applies(s) && k3_uses_package(s)) return k3_pack(s, w, wp, stream);
   if (k3_applies(s) || use_pointwise(s)) return launch_copy(w, wp, implicit_gemm_packed_bytes(s), stream);
+  if (use_nhwc(s)) return nhwc_layer_pack(s, w, wp, stream);
   if (ws_applies(s)) return ws_pack(s, w, wp, stream);
   return s.dtype == DT_F32 ? pack_typed<float>(s, w, wp, stream) : pack_typed<bf16_t>(s, w, wp, stream);
 }
@@ -1830,6 +1860,7 @@ hipError_t launch_implicit_main(const Shape& s, const void* x, const void* wp, c
                                 hipStream_t stream, const void* res) {
   if (rows_applies(s)) return rows_main(s, x, wp, b, y, stream, res);
   if (k3_applies(s)) return k3_main(s, x, wp, b, y, part, stream, res, true);
+  if (use_nhwc(s)) return nhwc_layer_main(s, x, wp, b, y, part, stream, res);
   if (ws_applies(s)) return ws_main(s, x, wp, b, y, part, stream, res);
   if (use_pointwise(s))
     return s.dtype == DT_F32 ? pw_main_typed<float>(s, x, wp, b, y, part, res, stream)
@@ -1874,6 +1905,7 @@ std::string implicit_gemm_describe(const Shape& s) {
     }
     return d;
   }
+  if (use_nhwc(s)) return nhwc_layer_describe(s);
   if (ws_applies(s)) return ws_describe(s);
   if (use_pointwise(s)) return s.dtype == DT_F32 ? pw_describe<float>(s) : pw_describe<bf16_t>(s);
   return s.dtype == DT_F32 ? describe_typed<float>(s) : describe_typed<bf16_t>(s);

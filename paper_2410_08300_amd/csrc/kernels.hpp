@@ -126,6 +126,16 @@ hipError_t launch_to_nhwc(int dtype, const void* x, void* y, int64_t N, int64_t 
 hipError_t nhwc_main(const Shape& s, const void* x, const void* pk, const void* b, void* y, const void* res,
                      bool out_nhwc, hipStream_t stream);
 
+// The same for a layer on N x C x H x W tensors: copy is nhwc_layer_bytes of
+// workspace, 256-byte aligned.
+bool nhwc_layer_applies(const Shape& s);
+size_t nhwc_layer_packed_bytes(const Shape& s);
+hipError_t nhwc_layer_pack(const Shape& s, const void* w, void* pk, hipStream_t stream);
+size_t nhwc_layer_bytes(const Shape& s);
+hipError_t nhwc_layer_main(const Shape& s, const void* x, const void* pk, const void* b, void* y, void* copy,
+                           hipStream_t stream, const void* res = nullptr);
+std::string nhwc_layer_describe(const Shape& s);
+
 // Implicit precomputed-index GEMM: the package holds the zero-padded
 // filters and the reduction and pixel index tables; no other workspace.
 bool precomp_applies(const Shape& s);

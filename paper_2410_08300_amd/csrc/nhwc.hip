@@ -693,8 +693,8 @@ bool nhwc_applies(const Shape& s) {
 size_t nhwc_packed_bytes(const Shape& s) { return (size_t)s.K * s.R * s.S * nh_units_per_pixel(s) * 16; }
 size_t nhwc_input_bytes(const Shape& s) { return (size_t)s.N * s.H * s.W * nh_units_per_pixel(s) * 16; }
 
-hipError_t nhwc_pack(const Shape& s, const void* w, void* pk, hipStream_t stream) {
-  const int CU = nh_units_per_pixel(s);
+namespace {
+hipError_t nh_pack(const Shape& s, const void* w, void* pk, int CU, hipStream_t stream) {
   const int64_t units = s.K * s.R * s.S * CU;
   const dim3 grid((unsigned)((units + 255) / 256));
   if (s.dtype == DT_F32)
@@ -706,9 +706,9 @@ hipError_t nhwc_pack(const Shape& s, const void* w, void* pk, hipStream_t stream
   return hipGetLastError();
 }
 
-hipError_t launch_to_nhwc(int dtype, const void* x, void* y, int64_t N, int64_t C, int64_t HW, hipStream_t stream) {
-  const int ue = dtype == DT_F32 ? 4 : 8, tc = 8 * ue;
-  const int CU = (int)((C + ue - 1) / ue), ptiles = (int)((HW + 63) / 64), ctiles = (int)((C + tc - 1) / tc);
+hipError_t nh_copy(int dtype, const void* x, void* y, int64_t N, int64_t C, int64_t HW, int CU, hipStream_t stream) {
+  const int ue = dtype == DT_F32 ? 4 : 8;
+  const int ptiles = (int)((HW + 63) / 64), ctiles = (CU + 7) / 8;
   const int vec = HW % ue == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
   const dim3 grid((unsigned)(N * ptiles * ctiles));
   if (dtype == DT_F32)
@@ -718,6 +718,83 @@ hipError_t launch_to_nhwc(int dtype, const void* x, void* y, int64_t N, int64_t 
     hipLaunchKernelGGL(to_nhwc_kernel<bf16_t>, grid, dim3(256), 0, stream, (const bf16_t*)x, (bf16_t*)y, (int)C,
                        (int)HW, CU, ptiles, ctiles, vec);
   return hipGetLastError();
+}
+}  // namespace
+
+hipError_t nhwc_pack(const Shape& s, const void* w, void* pk, hipStream_t stream) {
+  return nh_pack(s, w, pk, nh_units_per_pixel(s), stream);
+}
+
+hipError_t launch_to_nhwc(int dtype, const void* x, void* y, int64_t N, int64_t C, int64_t HW, hipStream_t stream) {
+  const int ue = dtype == DT_F32 ? 4 : 8;
+  return nh_copy(dtype, x, y, N, C, HW, (int)((C + ue - 1) / ue), stream);
+}
+
+// ---- single layers -----------------------------------------------------------
+// A layer called by itself takes N x C x H x W: a batch of its images is copied
+// to channels-last in the workspace, then convolved.  The copy and the filter
+// package together stay within 32 MiB (the static scratch, so no layer that ran
+// there is refused), in batches of equal size.
+namespace {
+constexpr size_t kLayerBytes = (size_t)32 << 20;
+}  // namespace
+
+// The layer with the channels its copy holds: C, or C rounded up to whole
+// 128-byte pieces where that adds at most a seventh (all lanes of a k-tile are
+// then on one tap, which saves each its own tap arithmetic).
+namespace {
+Shape nh_layer_shape(const Shape& s) {
+  const int64_t step = 128 / s.esize(), up = (s.C + step - 1) / step * step;
+  Shape b = s;
+  if ((up - s.C) * 7 <= s.C) b.C = b.Cg = up;
+  return b;
+}
+
+// Images per batch, 0 where one image does not fit.
+int64_t nh_layer_batch(const Shape& l) {
+  const size_t pk = align256(nhwc_packed_bytes(l));
+  const size_t img = (size_t)l.H * l.W * nh_units_per_pixel(l) * 16;
+  if (pk + img > kLayerBytes) return 0;
+  const int64_t nb = std::min<int64_t>(l.N, (int64_t)((kLayerBytes - pk) / img));
+  const int64_t batches = (l.N + nb - 1) / nb;
+  return (l.N + batches - 1) / batches;
+}
+}  // namespace
+
+bool nhwc_layer_applies(const Shape& s) {
+  if (s.dtype != DT_BF16 || s.N < 1 || s.G != 1) return false;
+  Shape l = nh_layer_shape(s);
+  l.N = nh_layer_batch(l);
+  return l.N >= 1 && nhwc_applies(l);
+}
+
+size_t nhwc_layer_packed_bytes(const Shape& s) { return nhwc_packed_bytes(nh_layer_shape(s)); }
+
+size_t nhwc_layer_bytes(const Shape& s) {
+  const Shape l = nh_layer_shape(s);
+  return align256((size_t)nh_layer_batch(l) * l.H * l.W * nh_units_per_pixel(l) * 16);
+}
+
+hipError_t nhwc_layer_pack(const Shape& s, const void* w, void* pk, hipStream_t stream) {
+  return nh_pack(s, w, pk, nh_units_per_pixel(nh_layer_shape(s)), stream);
+}
+
+hipError_t nhwc_layer_main(const Shape& s, const void* x, const void* pk, const void* b, void* y, void* copy,
+                           hipStream_t stream, const void* res) {
+  Shape l = nh_layer_shape(s);
+  const int64_t nb = nh_layer_batch(l);
+  if (nb < 1 || !copy) return hipErrorInvalidValue;
+  const int64_t in = s.C * s.H * s.W * s.esize(), out = s.K * s.P * s.Q * s.esize();
+  for (int64_t n0 = 0; n0 < s.N; n0 += nb) {
+    l.N = std::min(nb, s.N - n0);
+    hipError_t e = nh_copy(s.dtype, reinterpret_cast<const char*>(x) + n0 * in, copy, l.N, s.C, s.H * s.W,
+                           nh_units_per_pixel(l), stream);
+    if (e != hipSuccess) return e;
+    e = nhwc_main(l, copy, pk, b, reinterpret_cast<char*>(y) + n0 * out,
+                  res ? reinterpret_cast<const char*>(res) + n0 * out : nullptr, false, stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t nhwc_main(const Shape& s, const void* x, const void* pk, const void* b, void* y, const void* res,
@@ -743,6 +820,18 @@ hipError_t nhwc_main(const Shape& s, const void* x, const void* pk, const void* 
   const bool gen = CU % 8 != 0;
   return s.dtype == DT_F32 ? nh_dispatch<float>(a, cfg, gen, out_nhwc, stream)
                            : nh_dispatch<bf16_t>(a, cfg, gen, out_nhwc, stream);
+}
+
+std::string nhwc_layer_describe(const Shape& s) {
+  Shape l = nh_layer_shape(s);
+  l.N = nh_layer_batch(l);
+  const NhConfig& c = kNhConfigs[nh_config(l)];
+  char buf[256];
+  snprintf(buf, sizeof(buf),
+           "implicit_gemm kernels=nhwc_pack_kernel;to_nhwc_kernel;nhwc_conv_kernel<bf16> tile=%dx%d k_tiles=%d "
+           "images_per_launch=%lld (channels-last copy of the input, rows of pixels and filters copied to LDS by DMA)",
+           c.TJ, c.TI, (int)((s.R * s.S * nh_units_per_pixel(l) + 7) / 8), (long long)l.N);
+  return buf;
 }
 
 }  // namespace convsel

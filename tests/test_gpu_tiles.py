@@ -173,3 +173,43 @@ def test_channels_last_pooling(kind, c, hw, k):
     ref = net.cpu().double()(x.double()).detach().numpy()
     # five bf16 roundings, averaged over the plane
     assert np.abs(f64(y) - ref).max() <= 5 * 2.0 ** -8 * np.abs(ref).max()
+
+
+# N, C, H, W, K, R, stride, pad, dilation: single layers of the channels-last kernel.  Channels that fill their last
+# 16-byte unit or not, rounded up to whole 128-byte pieces or not; a copy that needs two batches of images; planes of
+# 8-, 4- and odd-pixel rows; the smallest work that takes this path.
+LAYERS = [
+    (3, 20, 15, 15, 24, 5, 1, 2, 1),
+    (2, 60, 21, 20, 72, 3, 1, 1, 1),
+    (2, 120, 16, 16, 64, 5, 2, 2, 1),
+    (4, 48, 14, 14, 40, 3, 1, 2, 2),
+    (1, 13, 33, 31, 17, 7, 2, 3, 1),
+    (130, 128, 36, 36, 8, 5, 2, 2, 1),
+    (7, 100, 33, 35, 72, 3, 1, 1, 1),
+    (1, 31, 27, 27, 33, 3, 1, 0, 1),
+]
+
+
+@pytest.mark.parametrize("case", LAYERS, ids=str)
+def test_channels_last_layer(case):
+    N, C, H, W, K, R, st, pad, dil = case
+    g = torch.Generator().manual_seed(C)
+    x = torch.randn(N, C, H, W, generator=g).to(torch.bfloat16)
+    w = (torch.randn(K, C, R, R, generator=g) / (C * R * R) ** 0.5).to(torch.bfloat16)
+    b = torch.randn(K, generator=g).to(torch.bfloat16)
+    say("channels-last layer", case)
+    d = cs.describe(x.shape, w.shape, st, pad, dil, 1, torch.bfloat16, "implicit_gemm", True, True)
+    assert "nhwc_conv_kernel" in d
+    kw = dict(stride=st, padding=pad, dilation=dil, algo="implicit_gemm", relu=True)
+    y = cs.conv2d(x.to(DEV), w.to(DEV), b.to(DEV), **kw)
+    pk = cs.pack_filters(w.to(DEV), tuple(x.shape), bias=True, **kw)
+    yp = cs.conv2d_prepacked(x.to(DEV), pk, tuple(w.shape), b.to(DEV), **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(y, yp)
+    ref = oracle.conv2d(f64(x), f64(w), f64(b), st, pad, dil, 1, True)
+    # fp32 sums of C*R*R terms, then one bf16 rounding
+    S = oracle.conv2d(np.abs(f64(x)), np.abs(f64(w)), np.abs(f64(b)), st, pad, dil, 1, False)
+    assert (np.abs(f64(y) - ref) <= (C * R * R + 1) * 2.0 ** -24 * S + 2.0 ** -8 * np.abs(ref) + 1e-30).all()
+    # never more workspace than the static scratch holds
+    assert cs._lib.workspace_bytes(cs._lib.make_desc(N, C, H, W, K, R, R, st, pad, dil, 1, "bf16", True, True),
+                                   "implicit_gemm") <= cs._lib.static_scratch_capacity()
