@@ -161,6 +161,9 @@ def status_string(status):
 
 
 def algo_id(name):
+    known = ALGOS.get(name) if isinstance(name, str) else None
+    if known is not None:
+        return known
     out = ctypes.c_int()
     st = lib().conv2d_algo_from_name(name.encode() if isinstance(name, str) else name, ctypes.byref(out))
     if st != CONV_OK:

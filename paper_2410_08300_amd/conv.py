@@ -4,6 +4,7 @@ PyTorch supplies device memory (caching allocator) and the current stream;
 the convolution itself runs in the HIP library.  Inputs must be CUDA (HIP)
 tensors: there is no CPU path.
 """
+import contextlib
 import ctypes
 
 import torch
@@ -11,6 +12,17 @@ import torch
 from . import _lib
 
 _TORCH_DTYPES = {torch.float32: "f32", torch.bfloat16: "bf16"}
+_NO_SWITCH = contextlib.nullcontext()
+
+
+def _on(device):
+    """Makes ``device`` current for a with block (nothing to do when it is)."""
+    return _NO_SWITCH if device.index == torch.cuda.current_device() else torch.cuda.device(device)
+
+
+def _stream_of(device):
+    """The handle of PyTorch's current stream on ``device``."""
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _desc_for(x, w, b, stride, padding, dilation, groups, relu):
@@ -48,7 +60,7 @@ def conv2d(x, w, b=None, stride=1, padding=0, dilation=1, groups=1, algo="defaul
     b = None if b is None else b.contiguous()
     P, Q = _lib.output_shape(desc)
     algo_i = _lib.algo_id(algo)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         if out is None:
             out = torch.empty((x.shape[0], w.shape[0], P, Q), device=x.device, dtype=x.dtype)
         elif (out.shape != (x.shape[0], w.shape[0], P, Q) or out.dtype != x.dtype or not out.is_contiguous()
@@ -57,7 +69,7 @@ def conv2d(x, w, b=None, stride=1, padding=0, dilation=1, groups=1, algo="defaul
                              % (x.dtype, (x.shape[0], w.shape[0], P, Q), x.device))
         nws = _lib.workspace_bytes(desc, algo_i)
         ws = torch.empty(nws, dtype=torch.uint8, device=x.device) if nws else None
-        stream = torch.cuda.current_stream(x.device).cuda_stream
+        stream = _stream_of(x.device)
         st = _lib.conv2d_raw(x.data_ptr(), w.data_ptr(), None if b is None else b.data_ptr(), out.data_ptr(),
                              desc, algo_i, None if ws is None else ws.data_ptr(), nws, stream)
     if st != _lib.CONV_OK:
@@ -73,9 +85,9 @@ def im2col(x, kernel_size, stride=1, padding=0, dilation=1, groups=1):
                           _TORCH_DTYPES[x.dtype])
     P, Q = _lib.output_shape(desc)
     x = x.contiguous()
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         col = torch.empty((N, groups, P * Q, (C // groups) * R * S), device=x.device, dtype=x.dtype)
-        st = _lib.im2col_raw(x.data_ptr(), col.data_ptr(), desc, torch.cuda.current_stream(x.device).cuda_stream)
+        st = _lib.im2col_raw(x.data_ptr(), col.data_ptr(), desc, _stream_of(x.device))
     if st != _lib.CONV_OK:
         raise _lib.Conv2dError(st, "conv2d_im2col")
     return col
@@ -86,9 +98,9 @@ def winograd_filter_transform(w):
     K, C, R, S = w.shape
     desc = _lib.make_desc(1, C, 4, 4, K, R, S, 1, 1, 1, 1, _TORCH_DTYPES[w.dtype])
     w = w.contiguous()
-    with torch.cuda.device(w.device):
+    with _on(w.device):
         u = torch.empty((16, K, C), device=w.device, dtype=w.dtype)
-        st = _lib.wino_filter_raw(w.data_ptr(), u.data_ptr(), desc, torch.cuda.current_stream(w.device).cuda_stream)
+        st = _lib.wino_filter_raw(w.data_ptr(), u.data_ptr(), desc, _stream_of(w.device))
     if st != _lib.CONV_OK:
         raise _lib.Conv2dError(st, "conv2d_winograd_filter_transform")
     return u
@@ -101,9 +113,9 @@ def winograd_input_transform(x, padding=1):
     P, Q = _lib.output_shape(desc)
     T = N * ((P + 1) // 2) * ((Q + 1) // 2)
     x = x.contiguous()
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         v = torch.empty((16, T, C), device=x.device, dtype=x.dtype)
-        st = _lib.wino_input_raw(x.data_ptr(), v.data_ptr(), desc, torch.cuda.current_stream(x.device).cuda_stream)
+        st = _lib.wino_input_raw(x.data_ptr(), v.data_ptr(), desc, _stream_of(x.device))
     if st != _lib.CONV_OK:
         raise _lib.Conv2dError(st, "conv2d_winograd_input_transform")
     return v
@@ -126,11 +138,11 @@ def pack_filters(w, x_shape, stride=1, padding=0, dilation=1, groups=1, algo="de
     algo_i = _lib.algo_id(algo)
     nbytes = _lib.packed_filter_bytes(desc, algo_i)
     w = w.contiguous()
-    with torch.cuda.device(w.device):
+    with _on(w.device):
         pk = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=w.device)
         st = _lib.lib().conv2d_pack_filters(ctypes.c_void_p(w.data_ptr()), ctypes.c_void_p(pk.data_ptr()),
                                             ctypes.byref(desc), algo_i,
-                                            ctypes.c_void_p(torch.cuda.current_stream(w.device).cuda_stream))
+                                            ctypes.c_void_p(_stream_of(w.device)))
     if st != _lib.CONV_OK:
         raise _lib.Conv2dError(st, "conv2d_pack_filters(algo=%s)" % _lib.algo_name(algo_i))
     return pk
@@ -152,7 +164,7 @@ def conv2d_prepacked(x, packed, w_shape, b=None, stride=1, padding=0, dilation=1
     b = None if b is None else b.contiguous()
     P, Q = _lib.output_shape(desc)
     algo_i = _lib.algo_id(algo)
-    with torch.cuda.device(x.device):
+    with _on(x.device):
         if out is None:
             out = torch.empty((N, K, P, Q), device=x.device, dtype=x.dtype)
         nws = _lib.prepacked_workspace_bytes(desc, algo_i)
@@ -161,7 +173,7 @@ def conv2d_prepacked(x, packed, w_shape, b=None, stride=1, padding=0, dilation=1
                                          ctypes.c_void_p(0 if b is None else b.data_ptr()),
                                          ctypes.c_void_p(out.data_ptr()), ctypes.byref(desc), algo_i,
                                          ctypes.c_void_p(0 if ws is None else ws.data_ptr()), nws,
-                                         ctypes.c_void_p(torch.cuda.current_stream(x.device).cuda_stream))
+                                         ctypes.c_void_p(_stream_of(x.device)))
     if st != _lib.CONV_OK:
         raise _lib.Conv2dError(st, "conv2d_prepacked(algo=%s)" % _lib.algo_name(algo_i))
     return out
@@ -196,7 +208,7 @@ def prepare(x, w, b=None, stride=1, padding=0, dilation=1, groups=1, algo="defau
     call = _lib.PreparedCall(x.data_ptr(), (pk if prepacked else w).data_ptr(),
                              None if b is None else b.data_ptr(), out.data_ptr(), desc, algo_i,
                              None if ws is None else ws.data_ptr(), nws,
-                             torch.cuda.current_stream(x.device).cuda_stream, prepacked=prepacked)
+                             _stream_of(x.device), prepacked=prepacked)
     call.workspace = ws  # keep alive
     call.package = pk
     return call, out

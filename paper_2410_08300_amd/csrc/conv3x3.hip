@@ -994,8 +994,7 @@ double k3_cost(const K3Plan& pl, const Shape& s) {
   return t;
 }
 
-bool make_k3_plan(const Shape& s, K3Plan& pl, int64_t N1 = -1, bool prepacked = false) {
-  if (!k3_shape_ok(s)) return false;
+bool search_k3_plan(const Shape& s, K3Plan& pl, int64_t N1, bool prepacked) {
   const int64_t img_bytes = s.C * s.H * s.W * 2;
   if (img_bytes > kMaxLaunchBytes) return false;
   if (N1 < 0) {
@@ -1056,6 +1055,32 @@ bool make_k3_plan(const Shape& s, K3Plan& pl, int64_t N1 = -1, bool prepacked = 
   // the kernel.
   pl = prepacked && best_has_pack ? best_pack : best_call;
   return true;
+}
+
+// The search builds some forty candidate plans (13 to 26 us on the host), and a
+// call asks for its layer's plan four or five times (support, workspace, launch);
+// the plan depends on the shape alone, so each thread remembers its last ones.
+bool make_k3_plan(const Shape& s, K3Plan& pl, int64_t N1 = -1, bool prepacked = false) {
+  if (!k3_shape_ok(s)) return false;
+  struct Entry {
+    bool used = false, found = false;
+    int64_t key[14];
+    K3Plan plan;
+  };
+  constexpr int kEntries = 64;
+  static thread_local Entry cache[kEntries];
+  const int64_t key[14] = {s.N, s.C, s.H, s.W, s.K, s.P, s.Q, s.sh, s.ph, s.pw, s.bias, s.relu, N1, prepacked};
+  uint64_t h = 0;
+  for (int64_t k : key) h = (h ^ (uint64_t)k) * 0x9E3779B97F4A7C15ull;
+  Entry& e = cache[(h >> 32) % kEntries];
+  if (!e.used || !std::equal(key, key + 14, e.key)) {
+    e.used = false;
+    e.found = search_k3_plan(s, e.plan, N1, prepacked);
+    std::copy(key, key + 14, e.key);
+    e.used = true;
+  }
+  if (e.found) pl = e.plan;
+  return e.found;
 }
 
 // Plan of a launch of `cnt` images with the tile shape and filter path of
