@@ -126,6 +126,13 @@ hipError_t launch_to_nhwc(int dtype, const void* x, void* y, int64_t N, int64_t 
 hipError_t nhwc_main(const Shape& s, const void* x, const void* pk, const void* b, void* y, const void* res,
                      bool out_nhwc, hipStream_t stream);
 
+// Direct depthwise 3 x 3 (stride 1 or 2) on channels-last tensors, C whole
+// 16-byte units.
+bool dw_nhwc_applies(const Shape& s);
+size_t dw_nhwc_packed_bytes(const Shape& s);
+hipError_t dw_nhwc_pack(const Shape& s, const void* w, void* pk, hipStream_t stream);
+hipError_t dw_nhwc_main(const Shape& s, const void* x, const void* pk, const void* b, void* y, hipStream_t stream);
+
 // The same for a layer on N x C x H x W tensors: copy is nhwc_layer_bytes of
 // workspace, 256-byte aligned.
 bool nhwc_layer_applies(const Shape& s);

@@ -108,17 +108,22 @@ __global__ __launch_bounds__(256) void global_avgpool_kernel(const T* __restrict
   if (lane == 0) elem<T>::store(y + plane, acc / static_cast<float>(HW));
 }
 
-// ---- the same on channels-last values (bf16, channels a multiple of 8) ------
+// ---- the same on channels-last values (channels whole 16-byte units) ------
 
 __device__ __forceinline__ float bf16_at(const vec16& v, int i) {
   return __uint_as_float((i & 1) ? (v.d[i >> 1] & 0xffff0000u) : (v.d[i >> 1] << 16));
 }
+template <typename T>
+__device__ __forceinline__ float unit_at(const vec16& v, int i) {
+  return elem<T>::to_f32(convsel::vec16_get<T>(v, i));
+}
 
-// One 16-byte unit (8 channels of one output pixel) per thread.
-template <bool MAX>
-__global__ __launch_bounds__(256) void pool_nhwc_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y, int H,
+// One 16-byte unit (8 bf16 or 4 fp32 channels of one output pixel) per thread.
+template <typename T, bool MAX>
+__global__ __launch_bounds__(256) void pool_nhwc_kernel(const T* __restrict__ x, T* __restrict__ y, int H,
                                                         int W, int P, int Q, int CU, int kh, int kw, int sh, int sw,
                                                         int ph, int pw, int64_t units) {
+  constexpr int UE = elem<T>::per16;
   const int64_t u = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   if (u >= units) return;
   const int cu = static_cast<int>(u % CU);
@@ -127,29 +132,26 @@ __global__ __launch_bounds__(256) void pool_nhwc_kernel(const bf16_t* __restrict
   const int64_t n = j / (static_cast<int64_t>(P) * Q);
   const int p = pq / Q, q = pq - p * Q;
   const int ih0 = p * sh - ph, iw0 = q * sw - pw;
-  const bf16_t* xn = x + (n * H * W * CU + cu) * 8;
-  float acc[8];
+  const T* xn = x + (n * H * W * CU + cu) * UE;
+  float acc[UE];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = MAX ? -INFINITY : 0.f;
+  for (int i = 0; i < UE; ++i) acc[i] = MAX ? -INFINITY : 0.f;
   for (int r = 0; r < kh; ++r) {
     const int ih = ih0 + r;
     if (ih < 0 || ih >= H) continue;
     for (int s = 0; s < kw; ++s) {
       const int iw = iw0 + s;
       if (iw < 0 || iw >= W) continue;
-      const vec16 v = convsel::load16(xn + (static_cast<int64_t>(ih) * W + iw) * CU * 8);
+      const vec16 v = convsel::load16(xn + (static_cast<int64_t>(ih) * W + iw) * CU * UE);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = MAX ? fmaxf(acc[i], bf16_at(v, i)) : acc[i] + bf16_at(v, i);
+      for (int i = 0; i < UE; ++i) acc[i] = MAX ? fmaxf(acc[i], unit_at<T>(v, i)) : acc[i] + unit_at<T>(v, i);
     }
   }
-  vec16 o;
+  vec16 o = convsel::vec16_zero();
+  const float k = static_cast<float>(kh * kw);
 #pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    const float k = static_cast<float>(kh * kw);
-    o.d[d] = MAX ? convsel::f32x2_to_bf16x2(acc[2 * d], acc[2 * d + 1])
-                 : convsel::f32x2_to_bf16x2(acc[2 * d] / k, acc[2 * d + 1] / k);
-  }
-  convsel::store16(y + u * 8, o);
+  for (int i = 0; i < UE; ++i) convsel::vec16_set<T>(o, i, elem<T>::from_f32(MAX ? acc[i] : acc[i] / k));
+  convsel::store16(y + u * UE, o);
 }
 
 // 3 x 3 pooling with stride 2 and padding 1 from N x C x H x W (W a multiple
@@ -217,29 +219,33 @@ __global__ __launch_bounds__(256) void pool3s2_to_nhwc_kernel(const bf16_t* __re
   convsel::store16(y + ((n * P + p) * Q + qo) * C + ct * 64 + cu * 8, v);
 }
 
-// Global average of N x HW x C: a workgroup takes 64 channels of one image,
-// 32 threads per 8 channels, summed through LDS in a fixed order.
-__global__ __launch_bounds__(256) void global_avgpool_nhwc_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y,
-                                                                  int HW, int CU, int ctiles) {
-  __shared__ float part[32][65];
+// Global average of N x HW x C: a workgroup takes 8 units of channels of one
+// image, 32 threads per unit, summed through LDS in a fixed order.
+template <typename T>
+__global__ __launch_bounds__(256) void global_avgpool_nhwc_kernel(const T* __restrict__ x, T* __restrict__ y, int HW,
+                                                                  int CU, int ctiles) {
+  constexpr int UE = elem<T>::per16;
+  __shared__ float part[32][8 * UE + 1];
   const int ct = blockIdx.x % ctiles;
   const int64_t n = blockIdx.x / ctiles;
   const int cl = threadIdx.x & 7, pl = threadIdx.x >> 3, cu = ct * 8 + cl;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float acc[UE];
+#pragma unroll
+  for (int k = 0; k < UE; ++k) acc[k] = 0.f;
   if (cu < CU)
     for (int i = pl; i < HW; i += 32) {
-      const vec16 v = convsel::load16(x + ((n * HW + i) * CU + cu) * 8);
+      const vec16 v = convsel::load16(x + ((n * HW + i) * CU + cu) * UE);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) acc[k] += bf16_at(v, k);
+      for (int k = 0; k < UE; ++k) acc[k] += unit_at<T>(v, k);
     }
 #pragma unroll
-  for (int k = 0; k < 8; ++k) part[pl][cl * 8 + k] = acc[k];
+  for (int k = 0; k < UE; ++k) part[pl][cl * UE + k] = acc[k];
   __syncthreads();
   const int c = threadIdx.x;
-  if (c >= 64 || ct * 64 + c >= CU * 8) return;
+  if (c >= 8 * UE || ct * 8 * UE + c >= CU * UE) return;
   float s = 0.f;
   for (int i = 0; i < 32; ++i) s += part[i][c];
-  elem<bf16_t>::store(y + n * CU * 8 + ct * 64 + c, s / static_cast<float>(HW));
+  elem<T>::store(y + n * CU * UE + ct * 8 * UE + c, s / static_cast<float>(HW));
 }
 
 unsigned blocks_for(int64_t n, int per = 256) { return static_cast<unsigned>((n + per - 1) / per); }
@@ -256,7 +262,7 @@ struct Value {
   int falias = -1;    // planned: a fused add's output shares its convolution's storage
   int64_t offset = -1;
   int64_t bytes = 0;
-  // planned: held channels-last (bf16 images between the convolutions of the
+  // planned: held channels-last (images between the convolutions of the
   // channels-last path), and the place of a channels-last copy of a value that
   // is not (-1: none), written just before its first reader cl_first
   bool cl = false;
@@ -378,36 +384,41 @@ hipError_t launch_elementwise(const Op& op, const void* a, const void* b, void* 
 }
 
 // Pooling and global average pooling with a channels-last value on either side.
+template <typename T>
 hipError_t launch_channels_last(const Op& op, const void* a, void* y, const Value& vin, const Value& vout, bool in_cl,
                                 hipStream_t st) {
-  const bf16_t* x = reinterpret_cast<const bf16_t*>(a);
-  bf16_t* o = reinterpret_cast<bf16_t*>(y);
+  const T* x = reinterpret_cast<const T*>(a);
+  T* o = reinterpret_cast<T*>(y);
+  constexpr int UE = elem<T>::per16;
   const int C = (int)vin.d[1], H = (int)vin.d[2], W = (int)vin.d[3];
   if (op.kind == OP_GAP) {
-    const int ctiles = (C + 63) / 64;
-    hipLaunchKernelGGL(global_avgpool_nhwc_kernel, dim3((unsigned)(vin.d[0] * ctiles)), dim3(256), 0, st, x, o, H * W,
-                       C / 8, ctiles);
+    const int ctiles = (C / UE + 7) / 8;
+    hipLaunchKernelGGL(global_avgpool_nhwc_kernel<T>, dim3((unsigned)(vin.d[0] * ctiles)), dim3(256), 0, st, x, o,
+                       H * W, C / UE, ctiles);
     return hipGetLastError();
   }
   const int P = (int)vout.d[2], Q = (int)vout.d[3];
   if (in_cl) {
-    const int64_t units = vout.elems() / 8;
+    const int64_t units = vout.elems() / UE;
     auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3(blocks_for(units)), dim3(256), 0, st, x, o, H, W, P, Q, C / 8, op.kh, op.kw, op.sh,
-                         op.sw, op.ph, op.pw, units);
+      hipLaunchKernelGGL(kern, dim3(blocks_for(units)), dim3(256), 0, st, x, o, H, W, P, Q, C / UE, op.kh, op.kw,
+                         op.sh, op.sw, op.ph, op.pw, units);
     };
-    if (op.pool_kind == 0) go(pool_nhwc_kernel<true>);
-    else go(pool_nhwc_kernel<false>);
+    if (op.pool_kind == 0) go(pool_nhwc_kernel<T, true>);
+    else go(pool_nhwc_kernel<T, false>);
     return hipGetLastError();
   }
-  const int qtiles = (Q + 31) / 32, ctiles = (C + 63) / 64;
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)(vin.d[0] * ctiles * P * qtiles)), dim3(256), 0, st, x, o, C, H, W, P, Q,
-                       qtiles, ctiles);
-  };
-  if (op.pool_kind == 0) go(pool3s2_to_nhwc_kernel<true>);
-  else go(pool3s2_to_nhwc_kernel<false>);
-  return hipGetLastError();
+  if constexpr (sizeof(T) == 2) {
+    const int qtiles = (Q + 31) / 32, ctiles = (C + 63) / 64;
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3((unsigned)(vin.d[0] * ctiles * P * qtiles)), dim3(256), 0, st, x, o, C, H, W, P, Q,
+                         qtiles, ctiles);
+    };
+    if (op.pool_kind == 0) go(pool3s2_to_nhwc_kernel<true>);
+    else go(pool3s2_to_nhwc_kernel<false>);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 }
 
 // A convolution of the channels-last path (operation number `index`): its
@@ -419,21 +430,22 @@ conv_status_t run_channels_last(const convsel_model& m, const Op& op, const void
     char* copy = m.arena + in.cl_offset;
     if (in.cl_first == index) {
       const conv_status_t s =
-          from_hip(convsel::launch_to_nhwc(convsel::DT_BF16, x, copy, op.shape.N, op.shape.C, op.shape.H * op.shape.W, st));
+          from_hip(convsel::launch_to_nhwc(op.shape.dtype, x, copy, op.shape.N, op.shape.C, op.shape.H * op.shape.W, st));
       if (s != CONV_OK) return s;
     }
     x = copy;
   }
   convsel::Shape s = op.shape;
   s.relu = op.relu_eff != 0;
-  return from_hip(convsel::nhwc_main(s, x, m.arena + op.pk_off, op.b ? m.arena + op.bias_off : nullptr, y, res,
-                                     m.vals[m.root(op.out)].cl, st));
+  const void* b = op.b ? m.arena + op.bias_off : nullptr;
+  if (s.G > 1) return from_hip(convsel::dw_nhwc_main(s, x, m.arena + op.pk_off, b, y, st));
+  return from_hip(convsel::nhwc_main(s, x, m.arena + op.pk_off, b, y, res, m.vals[m.root(op.out)].cl, st));
 }
 
-// Channels-last planning (bf16).  An implicit GEMM convolution (one group, C
-// and K multiples of 8) can run the channels-last kernel, which needs no
-// transposition of its input; a value between two such operations is then held
-// as N x H x W x C.  A value qualifies when everything that writes or reads it
+// Channels-last planning.  An implicit GEMM convolution (one group, C and K whole
+// 16-byte units) can run the channels-last kernel, which needs no transposition
+// of its input, and a direct depthwise 3 x 3 layer one of its own; a value
+// between two such operations is then held as N x H x W x C.  A value qualifies when everything that writes or reads it
 // can handle that: those convolutions, pooling, global average pooling, and
 // adds and ReLUs whose values all qualify; flattens only of 1 x 1 planes,
 // where the two layouts are the same.  The model's input and output stay N x C
@@ -449,7 +461,7 @@ void plan_layouts(convsel_model& m, int out_root) {
     v.cl_first = v.cl_last = -1;
   }
   for (Op& op : m.ops) op.cl = false;
-  if (m.dtype != CONV_BF16) return;
+  const int ue = m.dtype == CONV_F32 ? 4 : 8;
   std::vector<char> can(m.ops.size(), 0);  // convolutions the kernel serves
   auto plane1 = [&](int v) { return m.vals[v].ndim == 2 || m.vals[v].d[2] * m.vals[v].d[3] == 1; };
   for (size_t i = 0; i < m.ops.size(); ++i) {
@@ -462,17 +474,20 @@ void plan_layouts(convsel_model& m, int out_root) {
     s.N = d.n; s.C = d.c; s.H = d.h; s.W = d.w; s.K = d.k; s.R = d.r; s.S = d.s; s.P = P; s.Q = Q;
     s.G = d.groups; s.Cg = d.c / d.groups; s.Kg = d.k / d.groups;
     s.sh = d.stride_h; s.sw = d.stride_w; s.ph = d.pad_h; s.pw = d.pad_w; s.dh = d.dil_h; s.dw = d.dil_w;
-    s.dtype = convsel::DT_BF16;
+    s.dtype = m.dtype == CONV_F32 ? convsel::DT_F32 : convsel::DT_BF16;
     s.bias = d.has_bias != 0;
     s.relu = d.fuse_relu != 0;
-    can[i] = op.algo_run == CONV_ALGO_IMPLICIT_GEMM && s.C % 8 == 0 && s.K % 8 == 0 && convsel::nhwc_applies(s);
+    if (op.algo_run == CONV_ALGO_DIRECT)  // depthwise: both its values channels-last, or neither
+      can[i] = op.res < 0 && convsel::dw_nhwc_applies(s);
+    else
+      can[i] = op.algo_run == CONV_ALGO_IMPLICIT_GEMM && s.C % ue == 0 && s.K % ue == 0 && convsel::nhwc_applies(s);
   }
   // Candidates: storage roots, then those with an operation that cannot are
   // struck out until nothing changes.
   std::vector<char> cl(nv, 0);
   for (int v = 1; v < nv; ++v)
     cl[v] = m.vals[v].alias < 0 && m.vals[v].falias < 0 && v != out_root && m.vals[v].ndim == 4 &&
-            m.vals[v].d[1] % 8 == 0 && !plane1(v);
+            m.vals[v].d[1] % ue == 0 && !plane1(v);
   for (bool changed = true; changed;) {
     changed = false;
     auto strike = [&](int v) {
@@ -495,11 +510,13 @@ void plan_layouts(convsel_model& m, int out_root) {
           if (!can[i]) {
             strike(in);
             strike(out);
+          } else if (op.shape.G > 1) {
+            same(in, out);
           }
           if (op.res >= 0) same(m.root(op.res), out);
           break;
         case OP_POOL: {
-          const bool from_nchw = op.kh == 3 && op.kw == 3 && op.sh == 2 && op.sw == 2 && op.ph == 1 && op.pw == 1 &&
+          const bool from_nchw = m.dtype == CONV_BF16 && op.kh == 3 && op.kw == 3 && op.sh == 2 && op.sw == 2 && op.ph == 1 && op.pw == 1 &&
                                  m.vals[op.in].d[3] % 8 == 0 && in != 0;  // (pool3s2_to_nhwc_kernel)
           if (cl[in] && !cl[out] && !plane1(op.out)) strike(in);
           if (cl[out] && !cl[in] && !from_nchw) strike(out);
@@ -528,22 +545,27 @@ void plan_layouts(convsel_model& m, int out_root) {
   // a copy goes channels-last only with such planes in it, or when the copy is
   // small (2 MB: 3 us, where the many launches of a small batch matter more).
   int64_t copied = 0;
-  bool odd = false;
+  bool odd = false, depthwise = false;
   for (size_t i = 0; i < m.ops.size(); ++i) {
     const Op& op = m.ops[i];
     if (op.kind != OP_CONV || !can[i]) continue;
     const int in = m.root(op.in), out = m.root(op.out);
     if (!cl[in] && !cl[out]) continue;
-    if (!cl[in] && !plane1(op.in)) copied += m.vals[in].elems() * 2;
+    depthwise = depthwise || op.shape.G > 1;
+    if (!cl[in] && !plane1(op.in)) copied += m.vals[in].elems() * m.esize();
     odd = odd || op.shape.P * op.shape.Q % 8 != 0 || (op.shape.H * op.shape.W % 8 != 0 && op.shape.R == 1);
   }
-  if (copied > (2 << 20) && !odd) return;
+  // fp32 chains go channels-last around depthwise layers only (an inverted block,
+  // 96 -> 576 -> 96 of 14 x 14, 64 images: 87 us, channels-last 66).
+  if (m.dtype == CONV_F32 ? !depthwise : copied > (2 << 20) && !odd && !depthwise) return;
   for (int v = 0; v < nv; ++v) m.vals[v].cl = cl[v];
   for (size_t i = 0; i < m.ops.size(); ++i) {
     Op& op = m.ops[i];
     if (op.kind != OP_CONV || !can[i]) continue;
     const int in = m.root(op.in), out = m.root(op.out);
-    if (!cl[in] && !cl[out] && !(plane1(op.in) && in != 0 && op.shape.P * op.shape.Q == 1)) continue;
+    if (op.shape.G > 1 ? !cl[in]
+                       : !cl[in] && !cl[out] && !(plane1(op.in) && in != 0 && op.shape.P * op.shape.Q == 1))
+      continue;
     op.cl = true;
     if (!cl[in] && (!plane1(op.in) || in == 0)) {  // (the caller's tensor may not be 16-byte aligned)
       Value& v = m.vals[in];
@@ -555,7 +577,7 @@ void plan_layouts(convsel_model& m, int out_root) {
   // exists anyway (the projection of a residual block beside its first layer).
   for (size_t i = 0; i < m.ops.size(); ++i) {
     Op& op = m.ops[i];
-    if (op.kind != OP_CONV || !can[i] || op.cl) continue;
+    if (op.kind != OP_CONV || !can[i] || op.cl || op.shape.G > 1) continue;
     Value& v = m.vals[m.root(op.in)];
     if (v.cl_first < 0) continue;
     op.cl = true;
@@ -800,7 +822,7 @@ conv_status_t convsel_model_plan(convsel_model_t* model, int64_t n, int64_t c, i
     if (op.kind != OP_CONV) continue;
     size_t pk = 0, ws = 0;
     if (op.cl)
-      pk = convsel::nhwc_packed_bytes(op.shape);
+      pk = op.shape.G > 1 ? convsel::dw_nhwc_packed_bytes(op.shape) : convsel::nhwc_packed_bytes(op.shape);
     else if (conv2d_packed_filter_bytes(&op.desc, op.algo_run, &pk) != CONV_OK ||
              conv2d_prepacked_workspace_bytes(&op.desc, op.algo_run, &ws) != CONV_OK)
       return CONV_ERR_INVALID_ARG;
@@ -899,7 +921,8 @@ conv_status_t convsel_model_bind(convsel_model_t* model, void* arena, size_t are
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   for (Op& op : m.ops) {
     if (op.kind != OP_CONV) continue;
-    conv_status_t s = op.cl ? from_hip(convsel::nhwc_pack(op.shape, op.w, base + op.pk_off, st))
+    conv_status_t s = op.cl ? from_hip(op.shape.G > 1 ? convsel::dw_nhwc_pack(op.shape, op.w, base + op.pk_off, st)
+                                                      : convsel::nhwc_pack(op.shape, op.w, base + op.pk_off, st))
                             : conv2d_pack_filters(op.w, base + op.pk_off, &op.desc, op.algo_run, stream);
     if (s != CONV_OK) return s;
     if (op.b) {
@@ -949,7 +972,9 @@ conv_status_t convsel_model_forward(convsel_model_t* model, const void* x, void*
       case OP_POOL:
       case OP_GAP:
         if (m.vals[m.root(op.in)].cl || m.vals[m.root(op.out)].cl) {
-          s = from_hip(launch_channels_last(op, ptr(op.in), ptr(op.out), vin, vout, m.vals[m.root(op.in)].cl, st));
+          const bool in_cl = m.vals[m.root(op.in)].cl;
+          s = from_hip(m.dtype == CONV_F32 ? launch_channels_last<float>(op, ptr(op.in), ptr(op.out), vin, vout, in_cl, st)
+                                           : launch_channels_last<bf16_t>(op, ptr(op.in), ptr(op.out), vin, vout, in_cl, st));
           break;
         }
         [[fallthrough]];

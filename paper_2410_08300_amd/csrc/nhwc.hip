@@ -535,6 +535,94 @@ __global__ __launch_bounds__(256) void nhwc_pack_kernel(const T* __restrict__ w,
   store16(pk + u * UE, v);
 }
 
+// ---- depthwise 3 x 3 ------------------------------------------------------------
+// A thread owns one 16-byte unit of channels and PR x QN output pixels (two rows
+// at stride 1, one at stride 2; 7 or 4 columns): its input units are requested
+// together (pixels outside the image read zeros past the buffer) and each feeds
+// up to nine taps from registers.  Consecutive lanes take consecutive channel
+// units, so every access is whole lines.
+//
+// What bounds it: its bytes, and the one round trip of a thread's reads (576
+// channels of 14 x 14, 64 images, fp32, 58 MB: 15.9 us with 2 x 7 pixels a
+// thread, 19.0 with 2 x 4, 20.6 with 1 x 4; the N x C x H x W kernel takes 21.5).
+// Seven columns where they pad a row no more than four do.
+struct DwArgs {
+  const void* x;
+  const void* w;  // [9][C]
+  const void* b;
+  void* y;
+  uint32_t x_bytes;
+  int H, W, P, Q, CU, ph, pw, pstrips, qstrips, relu;
+  int64_t threads;
+};
+
+template <typename T, int ST, int QN>
+__global__ __launch_bounds__(256) void dw3_nhwc_kernel(DwArgs a) {
+  constexpr int UE = elem<T>::per16, PR = ST == 1 ? 2 : 1;
+  constexpr int IR = (PR - 1) * ST + 3, IC = (QN - 1) * ST + 3;
+  const int64_t id = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (id >= a.threads) return;
+  const int cu = static_cast<int>(id % a.CU);
+  int64_t rest = id / a.CU;
+  const int q0 = static_cast<int>(rest % a.qstrips) * QN;
+  rest /= a.qstrips;
+  const int p0 = static_cast<int>(rest % a.pstrips) * PR;
+  const int n = static_cast<int>(rest / a.pstrips);
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, a.x_bytes);
+  vec16 in[IR][IC];
+#pragma unroll
+  for (int i = 0; i < IR; ++i) {
+    const int h = p0 * ST - a.ph + i;
+    const bool hin = h >= 0 && h < a.H;
+#pragma unroll
+    for (int j = 0; j < IC; ++j) {
+      const int w = q0 * ST - a.pw + j;
+      const uint32_t off = static_cast<uint32_t>(((n * a.H + h) * a.W + w) * a.CU + cu) * 16;
+      in[i][j] = buf_load16(xr, hin && w >= 0 && w < a.W ? off : a.x_bytes, 0);
+    }
+  }
+  const T* wp = reinterpret_cast<const T*>(a.w) + cu * UE;
+  vec16 wt[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) wt[t] = load16(wp + static_cast<int64_t>(t) * a.CU * UE);
+  float bias[UE];
+#pragma unroll
+  for (int e = 0; e < UE; ++e) bias[e] = a.b ? elem<T>::load(reinterpret_cast<const T*>(a.b) + cu * UE + e) : 0.f;
+  T* y = reinterpret_cast<T*>(a.y);
+#pragma unroll
+  for (int i = 0; i < PR; ++i)
+#pragma unroll
+    for (int j = 0; j < QN; ++j) {
+      float acc[UE];
+#pragma unroll
+      for (int e = 0; e < UE; ++e) acc[e] = 0.f;
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+          for (int e = 0; e < UE; ++e)
+            acc[e] = fmaf(elem<T>::to_f32(vec16_get<T>(in[i * ST + r][j * ST + s], e)),
+                          elem<T>::to_f32(vec16_get<T>(wt[r * 3 + s], e)), acc[e]);
+      vec16 v = vec16_zero();
+#pragma unroll
+      for (int e = 0; e < UE; ++e) {
+        float f = acc[e] + bias[e];
+        if (a.relu) f = fmaxf(f, 0.f);
+        vec16_set<T>(v, e, elem<T>::from_f32(f));
+      }
+      const int p = p0 + i, q = q0 + j;
+      if (p < a.P && q < a.Q) store16(y + (((static_cast<int64_t>(n) * a.P + p) * a.Q + q) * a.CU + cu) * UE, v);
+    }
+}
+
+// Depthwise filters C x 1 x 3 x 3 as [9][C].
+template <typename T>
+__global__ __launch_bounds__(256) void dw3_pack_kernel(const T* __restrict__ w, T* __restrict__ pk, int C) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < 9 * C) pk[i] = w[(i % C) * 9 + i / C];
+}
+
 // N x C x HW to N x HW x Cp (zeros in the channels past C).  A workgroup
 // transposes 64 pixels x 64 (bf16) or 32 (fp32) channels through LDS: reads
 // run along the pixels, writes along the channels in 16-byte units.
@@ -600,18 +688,20 @@ uint32_t magic_of(int d) { return d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) 
 // at batch 32, each run with every tile; median error 3 to 5 percent).  The
 // sum over those layers with the tile this picks is 812 us; 811 with the best
 // measured one for each, 870 with the best single tile.
+// In fp32 the matrix instructions bound a k-tile (a sixteenth of the bf16 rate):
+// mfma32 is what one takes on a CU to itself.
 struct NhConfig {
   int TJ, TI, occ;
-  double base, through, latency, tile;
+  double base, through, latency, tile, mfma32;
 };
 constexpr NhConfig kNhConfigs[] = {
-    {128, 128, 2, 5.33, 0.05, 0.755, 2.08},  // two stages
-    {64, 128, 2, 4.62, 0.230, 0.369, 1.38},  // three stages
-    {64, 128, 3, 4.96, 0.293, 0.683, 0.91},  // two stages
-    {64, 64, 2, 3.26, 0.174, 0.243, 1.11},   // four stages
-    {64, 64, 5, 3.88, 0.174, 0.632, 0.64},   // two stages
-    {32, 32, 2, 3.3, 0.10, 0.18, 0.9},       // steps split over the waves, eight stages
-    {32, 32, 1, 3.8, 0.05, 0.06, 1.2},       // the same with four groups of waves
+    {128, 128, 2, 5.33, 0.05, 0.755, 2.08, 1.9},  // two stages
+    {64, 128, 2, 4.62, 0.230, 0.369, 1.38, 0.95},  // three stages
+    {64, 128, 3, 4.96, 0.293, 0.683, 0.91, 0.95},  // two stages
+    {64, 64, 2, 3.26, 0.174, 0.243, 1.11, 0.48},   // four stages
+    {64, 64, 5, 3.88, 0.174, 0.632, 0.64, 0.48},   // two stages
+    {32, 32, 2, 3.3, 0.10, 0.18, 0.9, 0.21},       // steps split over the waves, eight stages
+    {32, 32, 1, 3.8, 0.05, 0.06, 1.2, 0.21},       // the same with four groups of waves
 };
 constexpr int kNumNh = sizeof(kNhConfigs) / sizeof(kNhConfigs[0]);
 
@@ -629,7 +719,8 @@ int nh_config(const Shape& s) {
     const NhConfig& t = kNhConfigs[c];
     const int64_t units = ((npq + t.TJ - 1) / t.TJ) * ((s.K + t.TI - 1) / t.TI);
     const int64_t w = (units + 255) / 256;
-    const double us = t.base + std::max((double)w * nk * t.through, (double)((w + t.occ - 1) / t.occ) * nk * t.latency) +
+    const double through = s.dtype == DT_F32 ? std::max(t.through, t.mfma32) : t.through;
+    const double us = t.base + std::max((double)w * nk * through, (double)((w + t.occ - 1) / t.occ) * nk * t.latency) +
                       (double)w * t.tile;
     if (c == 0 || us < bt) {
       best = c;
@@ -728,6 +819,50 @@ hipError_t nhwc_pack(const Shape& s, const void* w, void* pk, hipStream_t stream
 hipError_t launch_to_nhwc(int dtype, const void* x, void* y, int64_t N, int64_t C, int64_t HW, hipStream_t stream) {
   const int ue = dtype == DT_F32 ? 4 : 8;
   return nh_copy(dtype, x, y, N, C, HW, (int)((C + ue - 1) / ue), stream);
+}
+
+// ---- depthwise 3 x 3 layers: x, y channels-last with C whole 16-byte units ----
+
+bool dw_nhwc_applies(const Shape& s) {
+  const int64_t ue = 16 / s.esize();
+  return s.G == s.C && s.K == s.C && s.R == 3 && s.S == 3 && s.dh == 1 && s.dw == 1 && s.sh == s.sw && s.sh <= 2 &&
+         s.C % ue == 0 && s.N >= 1 && s.N * s.H * s.W * s.C * s.esize() < ((int64_t)1 << 31) - 64 && s.C < (1 << 24);
+}
+
+size_t dw_nhwc_packed_bytes(const Shape& s) { return (size_t)9 * s.C * s.esize(); }
+
+hipError_t dw_nhwc_pack(const Shape& s, const void* w, void* pk, hipStream_t stream) {
+  const dim3 grid((unsigned)((9 * s.C + 255) / 256));
+  if (s.dtype == DT_F32)
+    hipLaunchKernelGGL(dw3_pack_kernel<float>, grid, dim3(256), 0, stream, (const float*)w, (float*)pk, (int)s.C);
+  else
+    hipLaunchKernelGGL(dw3_pack_kernel<bf16_t>, grid, dim3(256), 0, stream, (const bf16_t*)w, (bf16_t*)pk, (int)s.C);
+  return hipGetLastError();
+}
+
+hipError_t dw_nhwc_main(const Shape& s, const void* x, const void* pk, const void* b, void* y, hipStream_t stream) {
+  DwArgs a;
+  a.x = x; a.w = pk; a.b = b; a.y = y;
+  a.x_bytes = (uint32_t)(s.N * s.H * s.W * s.C * s.esize());
+  a.H = (int)s.H; a.W = (int)s.W; a.P = (int)s.P; a.Q = (int)s.Q;
+  a.CU = (int)(s.C * s.esize() / 16);
+  a.ph = s.ph; a.pw = s.pw;
+  a.pstrips = (int)(s.sh == 1 ? (s.P + 1) / 2 : s.P);
+  const bool wide = (s.Q + 6) / 7 * 7 <= (s.Q + 3) / 4 * 4;
+  a.qstrips = (int)(wide ? (s.Q + 6) / 7 : (s.Q + 3) / 4);
+  a.relu = s.relu ? 1 : 0;
+  a.threads = s.N * a.pstrips * a.qstrips * a.CU;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((a.threads + 255) / 256)), dim3(256), 0, stream, a);
+  };
+  auto typed = [&](auto t) {
+    using T = decltype(t);
+    if (s.sh == 1) wide ? go(dw3_nhwc_kernel<T, 1, 7>) : go(dw3_nhwc_kernel<T, 1, 4>);
+    else wide ? go(dw3_nhwc_kernel<T, 2, 7>) : go(dw3_nhwc_kernel<T, 2, 4>);
+  };
+  if (s.dtype == DT_F32) typed(0.f);
+  else typed(bf16_t{});
+  return hipGetLastError();
 }
 
 // ---- single layers -----------------------------------------------------------

@@ -213,3 +213,51 @@ def test_channels_last_layer(case):
     # never more workspace than the static scratch holds
     assert cs._lib.workspace_bytes(cs._lib.make_desc(N, C, H, W, K, R, R, st, pad, dil, 1, "bf16", True, True),
                                    "implicit_gemm") <= cs._lib.static_scratch_capacity()
+
+
+class Inverted(torch.nn.Module):
+    def __init__(self, c, mid, k, st, pad, res, more):
+        super().__init__()
+        self.a = torch.nn.Conv2d(c, mid, 1)
+        self.b = torch.nn.Conv2d(mid, mid, 3, st, pad, groups=mid)
+        self.c = torch.nn.Conv2d(mid, k, 1)
+        self.d = torch.nn.Conv2d(k, 20, 1)
+        self.res, self.more = res, more
+
+    def forward(self, x):
+        y = self.c(torch.relu(self.b(torch.relu(self.a(x)))))
+        if self.res:
+            y = y + x
+        return self.d(y) if self.more else y
+
+
+# N, C, mid, K, H, W, stride, pad, residual, further layer.  Depthwise strips of 2 x 4 (stride 1) and 1 x 4 (stride 2)
+# outputs with remainders, no padding and padding 2, one-row planes; fp32 tiles of the channels-last kernel.
+INVERTED = [
+    (2, 16, 40, 16, 7, 9, 1, 1, True, False),
+    (1, 8, 24, 16, 8, 5, 2, 1, False, True),
+    (3, 24, 72, 40, 13, 14, 2, 0, False, False),
+    (2, 32, 64, 32, 6, 11, 1, 2, False, True),
+    (1, 64, 200, 64, 4, 3, 1, 0, False, False),
+    (40, 32, 192, 32, 14, 14, 1, 1, True, False),
+    (70, 96, 576, 96, 7, 7, 1, 1, True, True),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", INVERTED, ids=str)
+def test_channels_last_depthwise(case, dtype):
+    N, C, mid, K, H, W, st, pad, res, more = case
+    torch.manual_seed(mid)
+    net = Inverted(C, mid, K, st, pad, res, more).to(TDT[dtype]).eval()
+    x = torch.randn(N, C, H, W).to(TDT[dtype])
+    model = cs.swap_backend(net.to(DEV), {"a": "implicit_gemm", "b": "direct", "c": "implicit_gemm",
+                                          "d": "implicit_gemm"})
+    say("channels-last depthwise", case, dtype)
+    y = model(x.to(DEV))
+    torch.cuda.synchronize()
+    assert model.describe().count("channels_last") >= 3
+    ref = net.cpu().double()(x.double()).detach().numpy()
+    # fp32: sums of at most 600 terms a layer; bf16: one rounding per layer and the add
+    tol = 600 * 2.0 ** -24 if dtype == "f32" else 4 * 2.0 ** -8
+    assert np.abs(f64(y) - ref).max() <= tol * np.abs(ref).max()
