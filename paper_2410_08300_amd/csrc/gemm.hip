@@ -216,23 +216,23 @@ __global__ __launch_bounds__(kThreads) void gemm_nt_kernel(GemmArgs g, int batch
 // 56 x 56 fp32 layer (Winograd, 16 products of 256 x 6272 x 256): 160 us with
 // the register-staged kernel above, 195 (four stages, 64 x 64), 130 (two
 // stages); the fp32 matrix units' own time is 86 us.
-template <int TJ, int TI, int WJ_>
+template <int TJ, int TI, int WJ_, int NST_>
 struct GemmDmaShape {
   static constexpr int WJ = WJ_;
   static constexpr int WI = 4 / WJ;
   static constexpr int MJ = TJ / WJ / 32, NI = TI / WI / 32;  // 32 x 32 blocks per wave
   static constexpr int ROWS = TJ + TI;
   static constexpr int STAGE = ROWS * 128;
-    static constexpr int NST = STAGE <= 24 * 1024 ? 2 : 3;
+    static constexpr int NST = NST_;
   static constexpr int NDMA = ROWS / 8 / 4;  // DMA instructions per wave and stage
   static_assert(WJ * WI == 4 && MJ >= 1 && NI >= 1 && TJ % 32 == 0 && TI % 32 == 0 && ROWS % 32 == 0, "tile");
   static_assert(NST * STAGE <= 160 * 1024 && NDMA * (NST - 1) <= 63, "stages");
 };
 
-template <typename T, int TJ, int TI, int WJ, bool OUT_F32>
+template <typename T, int TJ, int TI, int WJ, int NST_, bool OUT_F32>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs g, int njt, int nit, uint32_t a_bytes,
                                                        uint32_t b_bytes) {
-  using Sh = GemmDmaShape<TJ, TI, WJ>;
+  using Sh = GemmDmaShape<TJ, TI, WJ, NST_>;
   constexpr int MJ = Sh::MJ, NI = Sh::NI, NST = Sh::NST, NDMA = Sh::NDMA, STAGE = Sh::STAGE;
   constexpr int ES = elem<T>::bytes, UE = elem<T>::per16, BK = 128 / ES;  // a k-tile is 128 bytes of a row
   extern __shared__ __align__(16) vec16 smem[];
@@ -404,10 +404,10 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs g, int njt, int 
   }
 }
 
-template <typename T, int TJ, int TI, int WJ, bool OUT_F32>
+template <typename T, int TJ, int TI, int WJ, int NST_, bool OUT_F32>
 hipError_t launch_dma_tile(const GemmArgs& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t stream) {
-  using Sh = GemmDmaShape<TJ, TI, WJ>;
-  const auto kern = gemm_dma_kernel<T, TJ, TI, WJ, OUT_F32>;
+  using Sh = GemmDmaShape<TJ, TI, WJ, NST_>;
+  const auto kern = gemm_dma_kernel<T, TJ, TI, WJ, NST_, OUT_F32>;
   const size_t lds = (size_t)Sh::NST * Sh::STAGE;
   static bool attr = false;
   if (!attr) {
@@ -442,18 +442,22 @@ bool gemm_dma_ok(int dtype, const GemmArgs& g, uint32_t& a_bytes, uint32_t& b_by
 // matrix units (a sixteenth of the bf16 rate) fed at any size (VGG block, two
 // layers: 313 us against 322 to 383 with the larger tiles).  bf16: the largest
 // tile whose grid fills the CUs, with TI no wider than M needs; small problems
-// take the 64 x 64 tile.
+// take the 64 x 64 tile, and up to two workgroups per CU four stages (no more
+// would share a CU at two either, and the k-tiles in flight are what hides
+// their latency: 23 filters, 2350 pixels, 2160 terms, whole call 29 us with four
+// stages, 35 with two; 48 filters, 20000 pixels, 288 terms 19 and 21).
 template <typename T, bool OUT_F32>
 hipError_t launch_dma(const GemmArgs& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t stream) {
   auto wgs = [&](int tj, int ti) { return (int64_t)((g.N + tj - 1) / tj) * ((g.M + ti - 1) / ti) * g.batch; };
   const int mr = (g.M + 63) / 64 * 64;
   if constexpr (sizeof(T) == 2) {
-    if (mr >= 256 && wgs(128, 256) >= 240) return launch_dma_tile<T, 128, 256, 1, OUT_F32>(g, a_bytes, b_bytes, stream);
-    if (mr >= 128 && wgs(128, 128) >= 240) return launch_dma_tile<T, 128, 128, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
-    if (wgs(256, 64) >= 240) return launch_dma_tile<T, 256, 64, 4, OUT_F32>(g, a_bytes, b_bytes, stream);
-    if (wgs(128, 64) >= 240) return launch_dma_tile<T, 128, 64, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
+    if (mr >= 256 && wgs(128, 256) >= 240) return launch_dma_tile<T, 128, 256, 1, 3, OUT_F32>(g, a_bytes, b_bytes, stream);
+    if (mr >= 128 && wgs(128, 128) >= 240) return launch_dma_tile<T, 128, 128, 2, 3, OUT_F32>(g, a_bytes, b_bytes, stream);
+    if (wgs(256, 64) >= 240) return launch_dma_tile<T, 256, 64, 4, 3, OUT_F32>(g, a_bytes, b_bytes, stream);
+    if (wgs(128, 64) >= 240) return launch_dma_tile<T, 128, 64, 2, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
   }
-  return launch_dma_tile<T, 64, 64, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
+  if (wgs(64, 64) > 512) return launch_dma_tile<T, 64, 64, 2, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
+  return launch_dma_tile<T, 64, 64, 2, 4, OUT_F32>(g, a_bytes, b_bytes, stream);
 }
 
 template <typename T, int BM, int BN, bool OUT_F32, bool BKM>

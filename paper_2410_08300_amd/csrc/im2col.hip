@@ -219,9 +219,9 @@ bool im2col_tile(const Shape& s, Im2colTile& t) {
   return true;
 }
 
-// The same matrix for the remaining layers whose rows are whole units (input
-// rows too long, by dilation, for the LDS tile; very large filters): one
-// thread per 16-byte unit of a row, consecutive threads along the row; the UE
+// The same matrix for the remaining layers whose rows are whole units (small
+// matrices; input rows too long, by dilation, for the LDS tile; very large
+// filters): one thread per 16-byte unit of a row, consecutive threads along the row; the UE
 // input elements are gathered with the tap indices stepped incrementally.
 template <typename T>
 __global__ __launch_bounds__(256) void im2col_vec_kernel(Im2colArgs a, int64_t units) {
@@ -278,8 +278,15 @@ hipError_t launch_im2col(const Shape& s, const void* x, void* col, int64_t n0, i
   a.n0 = n0;
   a.rows = nb * s.G * s.P * s.Q;
   const int64_t crs = s.Cg * s.R * s.S;
+  // Small matrices (fewer than about 800,000 units, 13 MB) stay with the
+  // element gather below: a unit per thread fills the chip at once, where the
+  // LDS tiles are too few and pay their setup (with the GEMM, bf16, 3 x 3: one
+  // 64-channel 56 x 56 image, 3.6 MB, 12.0 us against 17.9; two of 32 channels of
+  // 100 x 100, 11.5 MB, 18.9 against 20.3; 32 of 256 channels of 14 x 14, 28.9 MB,
+  // 51 against 35).
+  const int ue = s.dtype == DT_F32 ? 4 : 8;
   Im2colTile t;
-  if (reinterpret_cast<uintptr_t>(col) % 16 == 0 && im2col_tile(s, t)) {
+  if (a.rows * crs / ue >= 800000 && reinterpret_cast<uintptr_t>(col) % 16 == 0 && im2col_tile(s, t)) {
     const int64_t blocks = nb * s.G * t.chunks * t.ptiles * t.qtiles;
     const size_t lds = (size_t)t.CC * t.plane * s.esize();
     if (blocks < ((int64_t)1 << 31)) {
@@ -290,7 +297,6 @@ hipError_t launch_im2col(const Shape& s, const void* x, void* col, int64_t n0, i
       return hipGetLastError();
     }
   }
-  const int ue = s.dtype == DT_F32 ? 4 : 8;
   if (crs % ue == 0 && reinterpret_cast<uintptr_t>(col) % 16 == 0) {
     const int64_t units = a.rows * (crs / ue);
     const int64_t blocks = std::min<int64_t>((units + 255) / 256, 65536);
