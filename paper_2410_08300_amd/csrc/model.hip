@@ -556,7 +556,7 @@ void plan_layouts(convsel_model& m, int out_root) {
     odd = odd || op.shape.P * op.shape.Q % 8 != 0 || (op.shape.H * op.shape.W % 8 != 0 && op.shape.R == 1);
   }
   // fp32 chains go channels-last around depthwise layers only (an inverted block,
-  // 96 -> 576 -> 96 of 14 x 14, 64 images: 87 us, channels-last 66).
+  // 96 -> 576 -> 96 of 14 x 14, 64 images: 87 us, channels-last 64).
   if (m.dtype == CONV_F32 ? !depthwise : copied > (2 << 20) && !odd && !depthwise) return;
   for (int v = 0; v < nv; ++v) m.vals[v].cl = cl[v];
   for (size_t i = 0; i < m.ops.size(); ++i) {
