@@ -442,6 +442,32 @@ conv_status_t run_channels_last(const convsel_model& m, const Op& op, const void
   return from_hip(convsel::nhwc_main(s, x, m.arena + op.pk_off, b, y, res, m.vals[m.root(op.out)].cl, st));
 }
 
+convsel::Shape shape_of(const conv2d_desc_t& d) {
+  int64_t P = 0, Q = 0;
+  conv2d_output_shape(&d, &P, &Q);
+  convsel::Shape s{};
+  s.N = d.n; s.C = d.c; s.H = d.h; s.W = d.w; s.K = d.k; s.R = d.r; s.S = d.s; s.P = P; s.Q = Q;
+  s.G = d.groups; s.Cg = d.c / d.groups; s.Kg = d.k / d.groups;
+  s.sh = d.stride_h; s.sw = d.stride_w; s.ph = d.pad_h; s.pw = d.pad_w; s.dh = d.dil_h; s.dw = d.dil_w;
+  s.dtype = d.dtype == CONV_F32 ? convsel::DT_F32 : convsel::DT_BF16;
+  s.bias = d.has_bias != 0;
+  s.relu = d.fuse_relu != 0;
+  return s;
+}
+
+// The default choice of a model's layer: the fitted tree's, but for stride 2
+// filters that the filter-row kernel serves implicit GEMM where the tree says
+// precomputed indices.  3 -> 64 channels of 224 x 224, 7 x 7 stride 2, bf16, 1 to
+// 64 images: 7.0 to 56 us against 10.7 to 83; not stride 4, whose rows it mostly
+// skips (3 -> 96 of 300 x 300, 16 images, 76 against 20).
+conv_algo_t default_of(const conv2d_desc_t& d) {
+  const conv_algo_t al = conv2d_default_algo(&d);
+  if (al == CONV_ALGO_IMPLICIT_PRECOMP_GEMM && d.stride_h == 2 && d.stride_w == 2 &&
+      conv2d_check(&d, CONV_ALGO_IMPLICIT_GEMM) == CONV_OK && convsel::rows_applies(shape_of(d)))
+    return CONV_ALGO_IMPLICIT_GEMM;
+  return al;
+}
+
 // Channels-last planning.  An implicit GEMM convolution (one group, C and K whole
 // 16-byte units) can run the channels-last kernel, which needs no transposition
 // of its input, and a direct depthwise 3 x 3 layer one of its own; a value
@@ -468,15 +494,8 @@ void plan_layouts(convsel_model& m, int out_root) {
     Op& op = m.ops[i];
     if (op.kind != OP_CONV) continue;
     const conv2d_desc_t& d = op.desc;
-    int64_t P = 0, Q = 0;
-    conv2d_output_shape(&d, &P, &Q);
-    convsel::Shape& s = op.shape;
-    s.N = d.n; s.C = d.c; s.H = d.h; s.W = d.w; s.K = d.k; s.R = d.r; s.S = d.s; s.P = P; s.Q = Q;
-    s.G = d.groups; s.Cg = d.c / d.groups; s.Kg = d.k / d.groups;
-    s.sh = d.stride_h; s.sw = d.stride_w; s.ph = d.pad_h; s.pw = d.pad_w; s.dh = d.dil_h; s.dw = d.dil_w;
-    s.dtype = m.dtype == CONV_F32 ? convsel::DT_F32 : convsel::DT_BF16;
-    s.bias = d.has_bias != 0;
-    s.relu = d.fuse_relu != 0;
+    op.shape = shape_of(d);
+    const convsel::Shape& s = op.shape;
     if (op.algo_run == CONV_ALGO_DIRECT)  // depthwise: both its values channels-last, or neither
       can[i] = op.res < 0 && convsel::dw_nhwc_applies(s);
     else
@@ -723,7 +742,7 @@ conv_status_t convsel_model_plan(convsel_model_t* model, int64_t n, int64_t c, i
           d = conv2d_desc_t{a.d[0], a.d[1], a.d[2], a.d[3], op.k, op.r, op.s, op.sh, op.sw, op.ph, op.pw,
                             op.dh, op.dw, op.groups, m.dtype, op.b != nullptr, op.relu};
         }
-        conv_algo_t al = op.algo == CONV_ALGO_DEFAULT ? conv2d_default_algo(&d) : op.algo;
+        conv_algo_t al = op.algo == CONV_ALGO_DEFAULT ? default_of(d) : op.algo;
         const conv_status_t st = conv2d_check(&d, al);
         if (st != CONV_OK) return st;
         op.algo_run = al;

@@ -246,3 +246,14 @@ def test_channels_last_plan():
     f32 = cs.swap_backend(nn.Sequential(nn.Conv2d(64, 16, 1), nn.Conv2d(16, 64, 1)), "implicit_gemm")
     f32._native.plan(2, 64, 14, 14)
     assert "channels_last" not in f32._native.describe()
+
+
+@pytest.mark.parametrize("stride,size,algo", [(2, 224, "implicit_gemm"), (4, 300, "implicit_precomp_gemm")])
+def test_default_choice_of_a_stem(stride, size, algo):
+    """A model's stride 2 stem of filter rows runs implicit GEMM by default; other layers keep the library's choice."""
+    net = nn.Sequential(nn.Conv2d(3, 64, 7, stride, 3)).to(torch.bfloat16)
+    m = cs.swap_backend(net)
+    m._native.plan(4, 3, size, size)
+    desc = _lib.make_desc(4, 3, size, size, 64, 7, 7, stride, 3, 1, 1, "bf16", True)
+    assert _lib.default_algo(desc) == "implicit_precomp_gemm"
+    assert "algo=%s" % algo in m._native.describe()
