@@ -292,7 +292,8 @@ struct Op {
   int res = -1;
   int relu_eff = 0;
   bool skip = false;
-  bool cl = false;  // planned: a convolution that runs the channels-last kernel
+  bool cl = false;    // planned: a convolution that runs the channels-last kernel
+  bool copy = false;  // planned: and reads its input's channels-last copy
   convsel::Shape shape{};
   conv2d_desc_t desc{};
   int64_t pk_off = -1, pk_bytes = 0, bias_off = -1, ws_bytes = 0;
@@ -425,8 +426,8 @@ hipError_t launch_channels_last(const Op& op, const void* a, void* y, const Valu
 // input's copy first, when this is the first operation that reads one.
 conv_status_t run_channels_last(const convsel_model& m, const Op& op, const void* x, const void* res, void* y,
                                 int index, hipStream_t st) {
-  const Value& in = m.vals[m.root(op.in)];
-  if (in.cl_offset >= 0) {
+  if (op.copy) {
+    const Value& in = m.vals[m.root(op.in)];
     char* copy = m.arena + in.cl_offset;
     if (in.cl_first == index) {
       const conv_status_t s =
@@ -486,10 +487,19 @@ void plan_layouts(convsel_model& m, int out_root) {
     v.cl_offset = -1;
     v.cl_first = v.cl_last = -1;
   }
-  for (Op& op : m.ops) op.cl = false;
+  for (Op& op : m.ops) op.cl = op.copy = false;
   const int ue = m.dtype == CONV_F32 ? 4 : 8;
   std::vector<char> can(m.ops.size(), 0);  // convolutions the kernel serves
   auto plane1 = [&](int v) { return m.vals[v].ndim == 2 || m.vals[v].d[2] * m.vals[v].d[3] == 1; };
+  // Operation i reads the channels-last copy of its input.  Never through a
+  // flatten, whose value is its root's storage in N x C x H x W order.
+  auto read_copy = [&](size_t i) {
+    Op& op = m.ops[i];
+    Value& v = m.vals[m.root(op.in)];
+    op.copy = true;
+    v.cl_first = v.cl_first < 0 ? (int)i : std::min(v.cl_first, (int)i);
+    v.cl_last = std::max(v.cl_last, (int)i);
+  };
   for (size_t i = 0; i < m.ops.size(); ++i) {
     Op& op = m.ops[i];
     if (op.kind != OP_CONV) continue;
@@ -586,22 +596,16 @@ void plan_layouts(convsel_model& m, int out_root) {
                        : !cl[in] && !cl[out] && !(plane1(op.in) && in != 0 && op.shape.P * op.shape.Q == 1))
       continue;
     op.cl = true;
-    if (!cl[in] && (!plane1(op.in) || in == 0)) {  // (the caller's tensor may not be 16-byte aligned)
-      Value& v = m.vals[in];
-      if (v.cl_first < 0) v.cl_first = (int)i;
-      v.cl_last = (int)i;
-    }
+    if (!cl[in] && (!plane1(op.in) || in == 0)) read_copy(i);  // (the caller's tensor may not be 16-byte aligned)
   }
   // A convolution between values that both stay as they are uses a copy that
   // exists anyway (the projection of a residual block beside its first layer).
   for (size_t i = 0; i < m.ops.size(); ++i) {
     Op& op = m.ops[i];
     if (op.kind != OP_CONV || !can[i] || op.cl || op.shape.G > 1) continue;
-    Value& v = m.vals[m.root(op.in)];
-    if (v.cl_first < 0) continue;
+    if (m.vals[op.in].ndim != 4 || m.vals[m.root(op.in)].cl_first < 0) continue;
     op.cl = true;
-    v.cl_first = std::min(v.cl_first, (int)i);
-    v.cl_last = std::max(v.cl_last, (int)i);
+    read_copy(i);
   }
 }
 
@@ -1026,8 +1030,7 @@ conv_status_t convsel_model_describe(const convsel_model_t* model, char* buf, si
     if (op.kind == OP_CONV) d += std::string(" algo=") + conv2d_algo_name(model->planned ? op.algo_run : op.algo);
     if (model->planned && op.cl) {
       d += " channels_last";
-      const Value& in = model->vals[model->root(op.in)];
-      if (in.cl_offset >= 0) d += " copy@" + std::to_string(in.cl_offset);
+      if (op.copy) d += " copy@" + std::to_string(model->vals[model->root(op.in)].cl_offset);
     }
     if (model->planned && op.res >= 0) d += " + v" + std::to_string(op.res);
     if (model->planned ? (op.kind == OP_CONV ? op.relu_eff : op.relu) : op.relu) d += " relu";

@@ -108,3 +108,18 @@ def randomize_bn(model, seed):
             m.weight.data.copy_(torch.rand(c, generator=g) + 0.5)
             m.bias.data.copy_(torch.randn(c, generator=g) * 0.1)
     return model.eval()
+
+
+class SharedFlatten(nn.Module):
+    """A value (the input, or its max-pool) read by a chain of convolutions and, flattened, by a linear layer."""
+
+    def __init__(self, pooled, c=64, hw=7):
+        super().__init__()
+        self.p = nn.MaxPool2d(2) if pooled else nn.Identity()
+        self.a, self.b = nn.Conv2d(c, 16, 1), nn.Conv2d(16, 32, 1)
+        self.gap = nn.AdaptiveAvgPool2d(1)
+        self.fc, self.aux = nn.Linear(32, 8), nn.Linear(c * hw * hw, 8)
+
+    def forward(self, x):
+        p = self.p(x)
+        return self.fc(torch.flatten(self.gap(self.b(self.a(p))), 1)) + self.aux(torch.flatten(p, 1))

@@ -12,7 +12,7 @@ from torch import nn
 import oracle
 import paper_2410_08300_amd as cs
 from paper_2410_08300_amd import _lib, backend
-from nets import ConvStack, ResNetSmall, randomize_bn
+from nets import ConvStack, ResNetSmall, SharedFlatten, randomize_bn
 
 
 def test_listing1_lowering_and_plan():
@@ -246,6 +246,16 @@ def test_channels_last_plan():
     f32 = cs.swap_backend(nn.Sequential(nn.Conv2d(64, 16, 1), nn.Conv2d(16, 64, 1)), "implicit_gemm")
     f32._native.plan(2, 64, 14, 14)
     assert "channels_last" not in f32._native.describe()
+
+
+@pytest.mark.parametrize("pooled", [True, False])
+def test_flattened_value_is_not_read_from_a_channels_last_copy(pooled):
+    """A linear layer reads a flattened image in place, also where the image has a channels-last copy."""
+    m = cs.swap_backend(SharedFlatten(pooled).to(torch.bfloat16), "implicit_gemm")
+    m._native.plan(2, 64, 14 if pooled else 7, 14 if pooled else 7)
+    d = m._native.describe().splitlines()
+    assert [line.split()[1] for line in d if "copy@" in line] == ["conv"]
+    assert sum(line.split()[1] == "linear" for line in d) == 2
 
 
 @pytest.mark.parametrize("stride,size,algo", [(2, 224, "implicit_gemm"), (4, 300, "implicit_precomp_gemm")])

@@ -7,6 +7,7 @@ import torch
 import oracle
 import paper_2410_08300_amd as cs
 from gpu_util import f64, say
+from nets import SharedFlatten
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -142,6 +143,22 @@ def test_channels_last_chain(case):
     ref = np.maximum(z + a, 0) if res else z
     # three bf16 roundings of fp32 sums on each side, the first two spread over sums of the later layers
     assert np.abs(f64(y) - ref).max() <= 3 * 2.0 ** -8 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("pooled", [True, False])
+def test_linear_beside_a_channels_last_copy(pooled):
+    """A linear layer on a flattened image that convolutions read as a channels-last copy."""
+    torch.manual_seed(5)
+    net = SharedFlatten(pooled).to(torch.bfloat16).eval()
+    x = torch.randn(2, 64, *((14, 14) if pooled else (7, 7))).to(torch.bfloat16)
+    say("linear beside a channels-last copy", pooled)
+    model = cs.swap_backend(net.to(DEV), "implicit_gemm")
+    y = model(x.to(DEV))
+    torch.cuda.synchronize()
+    assert "copy@" in model.describe()
+    ref = net.cpu().double()(x.double()).detach().numpy()
+    # five bf16 roundings of fp32 sums
+    assert np.abs(f64(y) - ref).max() <= 5 * 2.0 ** -8 * np.abs(ref).max()
 
 
 class Stem(torch.nn.Module):
