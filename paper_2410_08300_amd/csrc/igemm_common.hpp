@@ -535,7 +535,8 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 
 // LDS DMA for waves that also read the LDS themselves: copies 16 bytes per
 // lane from the buffer (offset voff per lane + soff) to lds + 16 * lane; lds
-// is the wave-uniform LDS byte address.  Offsets past the buffer copy zeros.
+// is the wave-uniform LDS byte address.  Offsets past the buffer copy zeros;
+// soff may be at most the buffer's size (the range check may subtract it).
 // The builtin form makes the compiler wait for every outstanding DMA
 // (s_waitcnt vmcnt(0)) before any LDS read of the wave, which undoes a ring
 // of stages; written out, the transfer has no register result and the waits

@@ -115,8 +115,8 @@ struct NhTile {
   static_assert((NB + NA) * (NST - 1) <= 63 && LDS <= 160 * 1024, "stages");
 };
 
-// GEN: a k-tile may span taps (Cp not a multiple of 128 bytes), so the tap is
-// a lane's own; otherwise all lanes are on one tap.
+// GEN: the tap is a lane's own and part of its offset; otherwise all lanes are on
+// one tap, whose offset is the DMA's scalar offset (nh_uniform_taps()).
 template <typename T, typename Tl, bool GEN, bool OUTC>
 __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
   constexpr int TJ = Tl::TJ, TI = Tl::TI, MJ = Tl::MJ, NI = Tl::NI, NB = Tl::NB, NA = Tl::NA, NST = Tl::NST;
@@ -731,6 +731,17 @@ int nh_units_per_pixel(const Shape& s) {
   return (int)((s.C + ue - 1) / ue);
 }
 
+// One tap for all lanes of a k-tile: where the tiles do not span taps (Cp whole
+// 128-byte pieces), and every tap's offset stays within the buffer.  The range
+// check that zeroes lanes outside the image may be made against the buffer's size
+// less the scalar offset, which must not go below zero.  Larger offsets belong to
+// taps outside the image for every pixel (padding of at least N * H rows).
+bool nh_uniform_taps(const Shape& s) {
+  const int64_t cu = nh_units_per_pixel(s);
+  const int64_t last = ((s.R - 1) * s.dh * s.W + (s.S - 1) * s.dw + 1) * cu - 8;
+  return cu % 8 == 0 && last <= (s.N * s.H * s.W + s.ph * s.W + s.pw) * cu;
+}
+
 int nh_config(const Shape& s) {
   const int64_t npq = s.N * s.P * s.Q;
   const double nk = (double)((s.R * s.S * nh_units_per_pixel(s) + 7) / 8);
@@ -973,7 +984,7 @@ hipError_t nhwc_main(const Shape& s, const void* x, const void* pk, const void* 
   a.nk = (a.ntap_units + 7) / 8;
   a.relu = s.relu ? 1 : 0;
   const int cfg = nh_config(s);
-  const bool gen = CU % 8 != 0;
+  const bool gen = !nh_uniform_taps(s);
   return s.dtype == DT_F32 ? nh_dispatch<float>(a, cfg, gen, out_nhwc, stream)
                            : nh_dispatch<bf16_t>(a, cfg, gen, out_nhwc, stream);
 }
@@ -985,8 +996,9 @@ std::string nhwc_layer_describe(const Shape& s) {
   char buf[256];
   snprintf(buf, sizeof(buf),
            "implicit_gemm kernels=nhwc_pack_kernel;to_nhwc_kernel;nhwc_conv_kernel<bf16> tile=%dx%d k_tiles=%d "
-           "images_per_launch=%lld (channels-last copy of the input, rows of pixels and filters copied to LDS by DMA)",
-           c.TJ, c.TI, (int)((s.R * s.S * nh_units_per_pixel(l) + 7) / 8), (long long)l.N);
+           "taps=%s images_per_launch=%lld (channels-last copy of the input, rows of pixels and filters copied to LDS by DMA)",
+           c.TJ, c.TI, (int)((s.R * s.S * nh_units_per_pixel(l) + 7) / 8),
+           nh_uniform_taps(l) ? "uniform" : "per_lane", (long long)l.N);
   return buf;
 }
 

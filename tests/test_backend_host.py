@@ -267,3 +267,18 @@ def test_default_choice_of_a_stem(stride, size, algo):
     desc = _lib.make_desc(4, 3, size, size, 64, 7, 7, stride, 3, 1, 1, "bf16", True)
     assert _lib.default_algo(desc) == "implicit_precomp_gemm"
     assert "algo=%s" % algo in m._native.describe()
+
+
+# C, H, W, R, pad, dilation, N: bf16 layers of the channels-last kernel, whose input buffer holds N*H*W pixels behind
+# pad rows and columns.
+@pytest.mark.parametrize("case", [(256, 14, 14, 3, 18, 18, 1), (256, 14, 14, 3, 18, 18, 2), (256, 14, 14, 3, 13, 13, 1),
+                                  (2048, 7, 7, 3, 12, 12, 1), (256, 14, 14, 3, 14, 14, 1), (512, 3, 4, 7, 3, 1, 1),
+                                  (512, 4, 3, 7, 3, 1, 1), (64, 28, 28, 5, 2, 1, 4), (64, 9, 30, 5, 16, 8, 1)], ids=str)
+def test_scalar_tap_offsets_stay_within_the_buffer(case):
+    C, H, W, R, pad, dil, N = case
+    d = cs.describe((N, C, H, W), (256, C, R, R), 1, pad, dil, 1, torch.bfloat16, "implicit_gemm")
+    assert "nhwc_conv_kernel" in d
+    pixel = 2 * C
+    last_tap = ((R - 1) * dil * W + (R - 1) * dil) * pixel + pixel - 128     # its last 128-byte piece
+    inside = last_tap <= (N * H * W + pad * W + pad) * pixel
+    assert ("taps=uniform" if inside else "taps=per_lane") in d

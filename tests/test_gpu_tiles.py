@@ -116,6 +116,7 @@ CHAINS = [
     (150, 128, 14, 14, 64, 3, 1, 1, 1, 128, False),
     (64, 64, 27, 27, 128, 1, 2, 0, 1, 256, True),
     (16, 8, 45, 45, 64, 3, 1, 1, 1, 512, False),
+    (1, 64, 2, 2, 64, 3, 2, 1, 1, 64, True),       # 3 x 3 on a 1 x 1 plane: taps past the whole buffer
 ]
 
 
@@ -206,6 +207,7 @@ LAYERS = [
     (130, 128, 36, 36, 8, 5, 2, 2, 1),
     (7, 100, 33, 35, 72, 3, 1, 1, 1),
     (1, 31, 27, 27, 33, 3, 1, 0, 1),
+    (1, 256, 14, 14, 64, 3, 1, 18, 18),       # dilation past the plane: taps past the whole buffer
 ]
 
 
