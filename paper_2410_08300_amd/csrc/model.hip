@@ -151,7 +151,7 @@ __global__ __launch_bounds__(256) void pool_nhwc_kernel(const T* __restrict__ x,
   const float k = static_cast<float>(kh * kw);
 #pragma unroll
   for (int i = 0; i < UE; ++i) convsel::vec16_set<T>(o, i, elem<T>::from_f32(MAX ? acc[i] : acc[i] / k));
-  convsel::store16(y + u * UE, o);
+  __builtin_memcpy(y + u * UE, &o, 16);  // (the caller's tensor: element alignment)
 }
 
 // 3 x 3 pooling with stride 2 and padding 1 from N x C x H x W (W a multiple
@@ -490,6 +490,9 @@ void plan_layouts(convsel_model& m, int out_root) {
   for (Op& op : m.ops) op.cl = op.copy = false;
   const int ue = m.dtype == CONV_F32 ? 4 : 8;
   std::vector<char> can(m.ops.size(), 0);  // convolutions the kernel serves
+  // The caller's tensors may have any element alignment: read through a copy,
+  // and by no kernel that takes 16-byte units of a plane.
+  auto callers = [&](int root) { return root == 0 || root == out_root; };
   auto plane1 = [&](int v) { return m.vals[v].ndim == 2 || m.vals[v].d[2] * m.vals[v].d[3] == 1; };
   // Operation i reads the channels-last copy of its input.  Never through a
   // flatten, whose value is its root's storage in N x C x H x W order.
@@ -546,7 +549,7 @@ void plan_layouts(convsel_model& m, int out_root) {
           break;
         case OP_POOL: {
           const bool from_nchw = m.dtype == CONV_BF16 && op.kh == 3 && op.kw == 3 && op.sh == 2 && op.sw == 2 && op.ph == 1 && op.pw == 1 &&
-                                 m.vals[op.in].d[3] % 8 == 0 && in != 0;  // (pool3s2_to_nhwc_kernel)
+                                 m.vals[op.in].d[3] % 8 == 0 && !callers(in);  // (pool3s2_to_nhwc_kernel)
           if (cl[in] && !cl[out] && !plane1(op.out)) strike(in);
           if (cl[out] && !cl[in] && !from_nchw) strike(out);
           break;
@@ -593,10 +596,11 @@ void plan_layouts(convsel_model& m, int out_root) {
     if (op.kind != OP_CONV || !can[i]) continue;
     const int in = m.root(op.in), out = m.root(op.out);
     if (op.shape.G > 1 ? !cl[in]
-                       : !cl[in] && !cl[out] && !(plane1(op.in) && in != 0 && op.shape.P * op.shape.Q == 1))
+                       : !cl[in] && !cl[out] &&
+                             !(plane1(op.in) && !callers(in) && op.shape.P * op.shape.Q == 1))
       continue;
     op.cl = true;
-    if (!cl[in] && (!plane1(op.in) || in == 0)) read_copy(i);  // (the caller's tensor may not be 16-byte aligned)
+    if (!cl[in] && (!plane1(op.in) || callers(in))) read_copy(i);
   }
   // A convolution between values that both stay as they are uses a copy that
   // exists anyway (the projection of a residual block beside its first layer).

@@ -282,3 +282,28 @@ def test_scalar_tap_offsets_stay_within_the_buffer(case):
     last_tap = ((R - 1) * dil * W + (R - 1) * dil) * pixel + pixel - 128     # its last 128-byte piece
     inside = last_tap <= (N * H * W + pad * W + pad) * pixel
     assert ("taps=uniform" if inside else "taps=per_lane") in d
+
+
+class OutputReadAgain(nn.Module):
+    """The model's output value is also read by a layer whose result is not used."""
+
+    def __init__(self, pool):
+        super().__init__()
+        self.a, self.b = nn.Conv2d(16, 32, 1), nn.Conv2d(32, 16, 1)
+        self.last = nn.AdaptiveAvgPool2d(1) if pool == "gap" else nn.MaxPool2d(7)
+        self.fc = nn.Linear(16, 8)
+
+    def forward(self, x):
+        y = torch.flatten(self.last(self.b(self.a(x))), 1)
+        self.fc(y)
+        return y
+
+
+@pytest.mark.parametrize("pool", ["gap", "max"])
+def test_layers_that_read_the_output_tensor_do_not_assume_its_alignment(pool):
+    """The channels-last kernel reads 16-byte units in place: of values in the arena only."""
+    m = cs.swap_backend(OutputReadAgain(pool).to(torch.bfloat16), "implicit_gemm")
+    m._native.plan(2, 16, 7, 7)
+    d = m._native.describe().splitlines()
+    assert sum("channels_last" in line for line in d) == 2
+    assert not any("channels_last" in line for line in d if line.split()[1] == "linear")

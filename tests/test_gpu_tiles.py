@@ -162,6 +162,31 @@ def test_linear_beside_a_channels_last_copy(pooled):
     assert np.abs(f64(y) - ref).max() <= 5 * 2.0 ** -8 * np.abs(ref).max()
 
 
+class EndsInPool(torch.nn.Module):
+    def __init__(self):
+        super().__init__()
+        self.a, self.b, self.pool = torch.nn.Conv2d(16, 32, 1), torch.nn.Conv2d(32, 16, 1), torch.nn.MaxPool2d(7)
+
+    def forward(self, x):
+        return self.pool(self.b(self.a(x)))
+
+
+def test_channels_last_pooling_into_an_unaligned_output():
+    """The output tensor of a model needs its elements' alignment only."""
+    torch.manual_seed(6)
+    net = EndsInPool().to(torch.bfloat16).eval()
+    x = torch.randn(3, 16, 7, 7).to(torch.bfloat16)
+    model = cs.swap_backend(net.to(DEV), "implicit_gemm")
+    xd = x.to(DEV)
+    y = model(xd)
+    assert model.describe().count("channels_last") == 2
+    room = torch.full((3 * 16 + 2,), 7.0, dtype=torch.bfloat16, device=DEV)
+    say("channels-last pooling into an unaligned output")
+    model._native.forward(xd.data_ptr(), room[1:].data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(room[1:-1].reshape(y.shape), y) and room[0] == 7 and room[-1] == 7
+
+
 class Stem(torch.nn.Module):
     def __init__(self, kind, k, c=64):
         super().__init__()
