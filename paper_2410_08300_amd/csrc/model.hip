@@ -220,7 +220,8 @@ __global__ __launch_bounds__(256) void pool3s2_to_nhwc_kernel(const bf16_t* __re
 }
 
 // Global average of N x HW x C: a workgroup takes 8 units of channels of one
-// image, 32 threads per unit, summed through LDS in a fixed order.
+// image, 32 threads per unit with two sums each, added up as a tree through LDS:
+// the order of global_avgpool_kernel, bit for bit.
 template <typename T>
 __global__ __launch_bounds__(256) void global_avgpool_nhwc_kernel(const T* __restrict__ x, T* __restrict__ y, int HW,
                                                                   int CU, int ctiles) {
@@ -229,23 +230,33 @@ __global__ __launch_bounds__(256) void global_avgpool_nhwc_kernel(const T* __res
   const int ct = blockIdx.x % ctiles;
   const int64_t n = blockIdx.x / ctiles;
   const int cl = threadIdx.x & 7, pl = threadIdx.x >> 3, cu = ct * 8 + cl;
-  float acc[UE];
+  float acc[2][UE];
 #pragma unroll
-  for (int k = 0; k < UE; ++k) acc[k] = 0.f;
+  for (int k = 0; k < UE; ++k) acc[0][k] = acc[1][k] = 0.f;
   if (cu < CU)
-    for (int i = pl; i < HW; i += 32) {
-      const vec16 v = convsel::load16(x + ((n * HW + i) * CU + cu) * UE);
+    for (int i = pl; i < HW; i += 64) {
+      const vec16 lo = convsel::load16(x + ((n * HW + i) * CU + cu) * UE);
+      const bool both = i + 32 < HW;
+      const vec16 hi = convsel::load16(x + ((n * HW + (both ? i + 32 : i)) * CU + cu) * UE);
 #pragma unroll
-      for (int k = 0; k < UE; ++k) acc[k] += unit_at<T>(v, k);
+      for (int k = 0; k < UE; ++k) {
+        acc[0][k] += unit_at<T>(lo, k);
+        acc[1][k] += both ? unit_at<T>(hi, k) : 0.f;
+      }
     }
 #pragma unroll
-  for (int k = 0; k < UE; ++k) part[pl][cl * UE + k] = acc[k];
+  for (int k = 0; k < UE; ++k) part[pl][cl * UE + k] = acc[0][k] + acc[1][k];
   __syncthreads();
   const int c = threadIdx.x;
   if (c >= 8 * UE || ct * 8 * UE + c >= CU * UE) return;
-  float s = 0.f;
-  for (int i = 0; i < 32; ++i) s += part[i][c];
-  elem<T>::store(y + n * CU * UE + ct * 8 * UE + c, s / static_cast<float>(HW));
+  float s[32];
+#pragma unroll
+  for (int i = 0; i < 32; ++i) s[i] = part[i][c];
+#pragma unroll
+  for (int m = 16; m >= 1; m >>= 1)
+#pragma unroll
+    for (int i = 0; i < m; ++i) s[i] += s[i + m];
+  elem<T>::store(y + n * CU * UE + ct * 8 * UE + c, s[0] / static_cast<float>(HW));
 }
 
 unsigned blocks_for(int64_t n, int per = 256) { return static_cast<unsigned>((n + per - 1) / per); }

@@ -162,6 +162,26 @@ def test_linear_beside_a_channels_last_copy(pooled):
     assert np.abs(f64(y) - ref).max() <= 5 * 2.0 ** -8 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("c,h,w", [(8, 2, 3), (40, 7, 7), (72, 8, 8), (64, 5, 13), (136, 33, 31)])
+def test_global_average_is_the_same_in_both_layouts(c, h, w, dtype):
+    """Sums of one order: a channels-last average equals the N x C x H x W one in every bit.  Layers that copy their
+    input (one filter tap of 1) put the averaged values in either layout."""
+    conv, dw = torch.nn.Conv2d(c, c, 1, bias=False), torch.nn.Conv2d(c, c, 3, 1, 1, groups=c, bias=False)
+    with torch.no_grad():
+        conv.weight.copy_(torch.eye(c)[:, :, None, None])
+        dw.weight.zero_()[:, :, 1, 1] = 1.0
+    net = torch.nn.Sequential(conv, dw, torch.nn.AdaptiveAvgPool2d(1)).to(TDT[dtype]).eval().to(DEV)
+    x = torch.randn(3, c, h, w, generator=torch.Generator().manual_seed(c)).to(TDT[dtype]).to(DEV)
+    last = cs.swap_backend(net, ["implicit_gemm", "direct"])
+    planes = cs.swap_backend(net, "direct")
+    say("global average in both layouts", c, h, w, dtype)
+    y, ref = last(x), planes(x)
+    torch.cuda.synchronize()
+    assert "channels_last" in last.describe() and "channels_last" not in planes.describe()
+    assert torch.equal(y, ref)
+
+
 class EndsInPool(torch.nn.Module):
     def __init__(self):
         super().__init__()
