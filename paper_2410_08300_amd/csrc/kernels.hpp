@@ -122,6 +122,7 @@ bool nhwc_applies(const Shape& s);
 size_t nhwc_packed_bytes(const Shape& s);
 size_t nhwc_input_bytes(const Shape& s);
 hipError_t nhwc_pack(const Shape& s, const void* w, void* pk, hipStream_t stream);
+std::string nhwc_describe(const Shape& s);  // tile, stages and tap form that nhwc_main takes
 hipError_t launch_to_nhwc(int dtype, const void* x, void* y, int64_t N, int64_t C, int64_t HW, hipStream_t stream);
 hipError_t nhwc_main(const Shape& s, const void* x, const void* pk, const void* b, void* y, const void* res,
                      bool out_nhwc, hipStream_t stream);

@@ -1045,6 +1045,10 @@ conv_status_t convsel_model_describe(const convsel_model_t* model, char* buf, si
     if (op.kind == OP_CONV) d += std::string(" algo=") + conv2d_algo_name(model->planned ? op.algo_run : op.algo);
     if (model->planned && op.cl) {
       d += " channels_last";
+      if (op.shape.G == 1) {
+        d += " " + convsel::nhwc_describe(op.shape);
+        d += model->vals[model->root(op.out)].cl ? " out=nhwc" : " out=planes";
+      }
       if (op.copy) d += " copy@" + std::to_string(model->vals[model->root(op.in)].cl_offset);
     }
     if (model->planned && op.res >= 0) d += " + v" + std::to_string(op.res);

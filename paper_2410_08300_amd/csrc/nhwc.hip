@@ -712,17 +712,18 @@ uint32_t magic_of(int d) { return d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) 
 // In fp32 the matrix instructions bound a k-tile (a sixteenth of the bf16 rate):
 // mfma32 is what one takes on a CU to itself.
 struct NhConfig {
-  int TJ, TI, occ;
+  int TJ, TI, WJ, WI, NST, G;  // NhTile
+  int occ;
   double base, through, latency, tile, mfma32;
 };
 constexpr NhConfig kNhConfigs[] = {
-    {128, 128, 2, 5.33, 0.05, 0.755, 2.08, 1.9},  // two stages
-    {64, 128, 2, 4.62, 0.230, 0.369, 1.38, 0.95},  // three stages
-    {64, 128, 3, 4.96, 0.293, 0.683, 0.91, 0.95},  // two stages
-    {64, 64, 2, 3.26, 0.174, 0.243, 1.11, 0.48},   // four stages
-    {64, 64, 5, 3.88, 0.174, 0.632, 0.64, 0.48},   // two stages
-    {32, 32, 2, 3.3, 0.10, 0.18, 0.9, 0.21},       // steps split over the waves, eight stages
-    {32, 32, 1, 3.8, 0.05, 0.06, 1.2, 0.21},       // the same with four groups of waves
+    {128, 128, 2, 2, 2, 1, 2, 5.33, 0.05, 0.755, 2.08, 1.9},
+    {64, 128, 2, 2, 3, 1, 2, 4.62, 0.230, 0.369, 1.38, 0.95},
+    {64, 128, 2, 2, 2, 1, 3, 4.96, 0.293, 0.683, 0.91, 0.95},
+    {64, 64, 2, 2, 4, 1, 2, 3.26, 0.174, 0.243, 1.11, 0.48},
+    {64, 64, 2, 2, 2, 1, 5, 3.88, 0.174, 0.632, 0.64, 0.48},
+    {32, 32, 1, 1, 8, 1, 2, 3.3, 0.10, 0.18, 0.9, 0.21},   // steps split over the waves
+    {32, 32, 1, 1, 4, 4, 1, 3.8, 0.05, 0.06, 1.2, 0.21},   // and k-tiles over four groups of waves
 };
 constexpr int kNumNh = sizeof(kNhConfigs) / sizeof(kNhConfigs[0]);
 
@@ -787,16 +788,23 @@ hipError_t nh_dispatch_tile(NhArgs& a, bool gen, bool outc, hipStream_t st) {
   return outc ? nh_launch<T, Tl, false, true>(a, st) : nh_launch<T, Tl, false, false>(a, st);
 }
 
+template <typename T, int I>
+hipError_t nh_dispatch_config(NhArgs& a, bool gen, bool outc, hipStream_t st) {
+  constexpr NhConfig c = kNhConfigs[I];
+  return nh_dispatch_tile<T, NhTile<T, c.TJ, c.TI, c.WJ, c.WI, c.NST, c.G>>(a, gen, outc, st);
+}
+
 template <typename T>
 hipError_t nh_dispatch(NhArgs& a, int cfg, bool gen, bool outc, hipStream_t st) {
+  static_assert(kNumNh == 7, "one line each");
   switch (cfg) {
-    case 0: return nh_dispatch_tile<T, NhTile<T, 128, 128, 2, 2, 2>>(a, gen, outc, st);
-    case 1: return nh_dispatch_tile<T, NhTile<T, 64, 128, 2, 2, 3>>(a, gen, outc, st);
-    case 2: return nh_dispatch_tile<T, NhTile<T, 64, 128, 2, 2, 2>>(a, gen, outc, st);
-    case 3: return nh_dispatch_tile<T, NhTile<T, 64, 64, 2, 2, 4>>(a, gen, outc, st);
-    case 4: return nh_dispatch_tile<T, NhTile<T, 64, 64, 2, 2, 2>>(a, gen, outc, st);
-    case 5: return nh_dispatch_tile<T, NhTile<T, 32, 32, 1, 1, 8>>(a, gen, outc, st);
-    case 6: return nh_dispatch_tile<T, NhTile<T, 32, 32, 1, 1, 4, 4>>(a, gen, outc, st);
+    case 0: return nh_dispatch_config<T, 0>(a, gen, outc, st);
+    case 1: return nh_dispatch_config<T, 1>(a, gen, outc, st);
+    case 2: return nh_dispatch_config<T, 2>(a, gen, outc, st);
+    case 3: return nh_dispatch_config<T, 3>(a, gen, outc, st);
+    case 4: return nh_dispatch_config<T, 4>(a, gen, outc, st);
+    case 5: return nh_dispatch_config<T, 5>(a, gen, outc, st);
+    case 6: return nh_dispatch_config<T, 6>(a, gen, outc, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -989,16 +997,22 @@ hipError_t nhwc_main(const Shape& s, const void* x, const void* pk, const void* 
                            : nh_dispatch<bf16_t>(a, cfg, gen, out_nhwc, stream);
 }
 
+std::string nhwc_describe(const Shape& s) {
+  const NhConfig& c = kNhConfigs[nh_config(s)];
+  char buf[96];
+  snprintf(buf, sizeof(buf), "tile=%dx%d stages=%d groups=%d taps=%s", c.TJ, c.TI, c.NST, c.G,
+           nh_uniform_taps(s) ? "uniform" : "per_lane");
+  return buf;
+}
+
 std::string nhwc_layer_describe(const Shape& s) {
   Shape l = nh_layer_shape(s);
   l.N = nh_layer_batch(l);
-  const NhConfig& c = kNhConfigs[nh_config(l)];
-  char buf[256];
+  char buf[384];
   snprintf(buf, sizeof(buf),
-           "implicit_gemm kernels=nhwc_pack_kernel;to_nhwc_kernel;nhwc_conv_kernel<bf16> tile=%dx%d k_tiles=%d "
-           "taps=%s images_per_launch=%lld (channels-last copy of the input, rows of pixels and filters copied to LDS by DMA)",
-           c.TJ, c.TI, (int)((s.R * s.S * nh_units_per_pixel(l) + 7) / 8),
-           nh_uniform_taps(l) ? "uniform" : "per_lane", (long long)l.N);
+           "implicit_gemm kernels=nhwc_pack_kernel;to_nhwc_kernel;nhwc_conv_kernel<bf16> %s k_tiles=%d "
+           "images_per_launch=%lld (channels-last copy of the input, rows of pixels and filters copied to LDS by DMA)",
+           nhwc_describe(l).c_str(), (int)((s.R * s.S * nh_units_per_pixel(l) + 7) / 8), (long long)l.N);
   return buf;
 }
 

@@ -12,6 +12,7 @@ from torch import nn
 import oracle
 import paper_2410_08300_amd as cs
 from paper_2410_08300_amd import _lib, backend
+import variants
 from nets import ConvStack, ResNetSmall, SharedFlatten, randomize_bn
 
 
@@ -307,3 +308,44 @@ def test_layers_that_read_the_output_tensor_do_not_assume_its_alignment(pool):
     d = m._native.describe().splitlines()
     assert sum("channels_last" in line for line in d) == 2
     assert not any("channels_last" in line for line in d if line.split()[1] == "linear")
+
+
+def test_variant_cases_cover_what_is_dispatched():
+    """Every variant of the channels-last convolution that random shapes reach is reached by a case of variants.py
+    (whose results the GPU tests check), in each dtype, tile, tap form and output layout."""
+    covered = set()
+    for case in variants.CASES:
+        m = variants.lower(case, variants.Pair(*case))
+        m._native.plan(*case[1:5])
+        covered |= variants.reached(case, m._native.describe())
+    tiles = {v[:5] for v in covered}
+    bf16 = {("128x128", "2", "1"), ("64x128", "3", "1"), ("64x128", "2", "1"), ("64x64", "4", "1"), ("64x64", "2", "1"),
+            ("32x32", "8", "1"), ("32x32", "4", "4")}
+    assert {v[1:4] for v in tiles if v[0] == "bf16"} == bf16
+    assert len({v for v in tiles if v[0] == "bf16"}) == 2 * len(bf16)
+    rng = np.random.default_rng(1)
+    seen, plans = set(), 0
+
+    def size(lo, hi):
+        return int(round(np.exp(rng.uniform(np.log(lo), np.log(hi)))))
+
+    while plans < 3000:
+        dtype = "bf16" if rng.random() < 0.6 else "f32"
+        unit = 8 if dtype == "bf16" else 4
+        n, c, k, k2 = size(1, 128), size(1, 60) * unit, size(1, 60) * unit, size(1, 60) * unit
+        c, k = (8 * v if rng.random() < 0.4 else v for v in (c, k))
+        r, r2, h, stride = rng.choice((1, 1, 3, 5)), rng.choice((1, 1, 3)), size(3, 60), rng.choice((1, 1, 2))
+        m = _lib.NativeModel(dtype)
+        case = (dtype, n, c, h, h + 1, k, int(r), int(stride), int(r) // 2, 1, k2, int(r2))
+        v = m.conv(0, c, k, r, r, (stride, stride), (r // 2, r // 2), (1, 1), 1, "implicit_gemm", 256, 256, True)
+        if dtype == "f32":
+            v = m.conv(v, k, k, 3, 3, (1, 1), (1, 1), (1, 1), k, "direct", 256, 256, True)
+        v = m.conv(v, k, k2, r2, r2, (1, 1), (r2 // 2, r2 // 2), (1, 1), 1, "implicit_gemm", 256, 256, True)
+        m.set_output(v)
+        try:
+            m.plan(n, c, h, h + 1)
+        except _lib.Conv2dError:
+            continue
+        seen |= variants.reached(case, m.describe())
+        plans += 1
+    assert len(seen) > 60 and seen <= covered, sorted(seen - covered)

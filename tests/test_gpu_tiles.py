@@ -6,6 +6,7 @@ import torch
 
 import oracle
 import paper_2410_08300_amd as cs
+import variants
 from gpu_util import f64, say
 from nets import SharedFlatten
 
@@ -100,9 +101,8 @@ class Chain(torch.nn.Module):
         return torch.relu(z + y) if self.res else z
 
 
-# N, C, H, W, K, R, stride, pad, dilation, K2, residual.  Together the plans reach every tile (128 x 128 to 32 x 32,
-# two to eight stages, one and four wave groups), both tap modes (C whole 128-byte pieces or not), and output rows of
-# 8, 4 and single pixels; 4 bytes' worth of copy and a plane of odd size each make the chain channels-last.
+# N, C, H, W, K, R, stride, pad, dilation, K2, residual: filters, strides, dilations and residuals on the smaller
+# tiles (variants.py reaches every tile); a small copy and a plane of odd size each make the chain channels-last.
 CHAINS = [
     (1, 64, 14, 14, 64, 3, 1, 1, 1, 128, True),
     (3, 72, 15, 16, 40, 3, 2, 1, 1, 64, True),
@@ -205,6 +205,36 @@ def test_channels_last_pooling_into_an_unaligned_output():
     model._native.forward(xd.data_ptr(), room[1:].data_ptr(), torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     assert torch.equal(room[1:-1].reshape(y.shape), y) and room[0] == 7 and room[-1] == 7
+
+
+@pytest.mark.parametrize("case", variants.CASES, ids=str)
+def test_channels_last_variants(case):
+    dtype, n, c, h, w = case[:5]
+    torch.manual_seed(c + 3 * case[5])
+    net = variants.Pair(*case).eval()
+    x = torch.randn(n, c, h, w).to(TDT[dtype])
+    say("channels-last variant", case)
+    model = variants.lower(case, net.to(DEV))
+    y = model(x.to(DEV))
+    torch.cuda.synchronize()
+    assert model.describe().count("channels_last") >= 2
+    net = net.cpu()
+
+    def conv(v, m, relu):
+        v = torch.nn.functional.conv2d(v, m.weight.double(), m.bias.double(), m.stride, m.padding, m.dilation,
+                                       m.groups)
+        return (v.relu() if relu else v).to(TDT[dtype]).double()  # values are stored in the data type
+
+    with torch.no_grad():
+        ref = conv(x.double(), net.a, True)
+        if dtype == "f32":
+            ref = conv(ref, net.dw, True)
+        ref = conv(ref, net.b, False)
+        if net.res:
+            ref = torch.relu(ref + x.double())
+    # bf16: three roundings on each side; fp32: sums of at most 600 terms a layer
+    tol = 3 * 2.0 ** -8 if dtype == "bf16" else 600 * 2.0 ** -24
+    assert np.abs(f64(y) - ref.numpy()).max() <= tol * ref.abs().max().item()
 
 
 class Stem(torch.nn.Module):
