@@ -449,9 +449,36 @@ __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
 #pragma unroll
       for (int it = 0; it < PASSES; ++it)
         if (RPI * it < left) store16(y + o0 + it * step, d[it]);
+    } else if (a.PQ % (sizeof(T) == 2 ? 4 : UE) != 0) {
+      // Planes of no whole units: one pixel per lane, so that a wave's stores run
+      // along a channel's pixels.  (Eight pixels of a lane one after the other
+      // instead, a store's lanes 16 bytes apart: 4 -> 126 channels, 2 x 2, 55
+      // images of 47 x 47 outputs, whole layer 47.7 us, this way 24.1.)
+      constexpr int LPX = COLS < 64 ? COLS : 64, RL = 64 / LPX;  // lanes along a row, rows per pass
+      const int left = a.K - rbase - lane / LPX;
+#pragma unroll
+      for (int cb = 0; cb < COLS; cb += LPX) {
+        const int col = cb + lane % LPX, j = j0 + wj * MJ * 32 + col;
+        if (j >= a.NPQ) continue;
+        const int n = j / a.PQ;
+        const int64_t o0 = (static_cast<int64_t>(n) * a.K + rbase + lane / LPX) * a.PQ + (j - n * a.PQ);
+#pragma unroll
+        for (int it = 0; it < ROWS / RL; ++it) {
+          if (RL * it >= left) break;
+          const int row = lane / LPX + RL * it;
+          const int64_t o = o0 + static_cast<int64_t>(RL * it) * a.PQ;
+          float f = elem<T>::load(reinterpret_cast<const T*>(
+              stg + row * (U * 16) + (((col / UE) ^ (row & (U - 1))) << 4) + (col % UE) * ES));
+          if (res) {
+            f += elem<T>::load(res + o);
+            if (a.relu) f = fmaxf(f, 0.f);
+          }
+          elem<T>::store(y + o, f);
+        }
+      }
     } else {
-      // UE consecutive pixels of a channel: whole units where the planes are
-      // whole units (one image), else pixel by pixel.
+      // UE consecutive pixels of a channel: a whole unit of one image, or (bf16,
+      // planes of whole half units) two halves.
       if (cbase >= a.NPQ) return;
       const int n = cbase / a.PQ, pq = cbase - n * a.PQ;
       const int64_t o0 = (static_cast<int64_t>(n) * a.K + rbase + rrow) * a.PQ + pq;
@@ -471,7 +498,7 @@ __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
 #pragma unroll
         for (int it = 0; it < PASSES; ++it)  // (the caller's tensor: element alignment)
           if (RPI * it < left) __builtin_memcpy(y + o0 + it * step, &d[it], 16);
-      } else if (sizeof(T) == 2 && a.PQ % 4 == 0) {
+      } else if constexpr (sizeof(T) == 2) {
         // Two half units of four pixels, each in one image.
         int64_t o[2];
         bool in[2];
@@ -498,35 +525,6 @@ __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
 #pragma unroll
           for (int h = 0; h < 2; ++h)
             if (RPI * it < left && in[h]) __builtin_memcpy(y + o[h] + it * step, &d[it].d[2 * h], 8);
-      } else {
-        const int64_t next_img = static_cast<int64_t>(a.K - 1) * a.PQ;
-#pragma unroll 1
-        for (int it = 0; it < PASSES; ++it) {
-          if (RPI * it >= left) break;
-          const vec16 dv = *reinterpret_cast<const vec16*>(stg + (rrow + RPI * it) * (U * 16) +
-                                                           ((u ^ ((rrow + RPI * it) & (U - 1))) << 4));
-          int64_t o = o0 + it * step;
-          int q = pq;
-#pragma unroll
-          for (int t = 0; t < UE; ++t) {
-            if (cbase + t >= a.NPQ) break;
-            float f;
-            if constexpr (sizeof(T) == 2)
-              f = __uint_as_float((t & 1) ? (dv.d[t >> 1] & 0xffff0000u) : (dv.d[t >> 1] << 16));
-            else
-              f = __uint_as_float(dv.d[t]);
-            if (res) {
-              f += elem<T>::load(res + o);
-              if (a.relu) f = fmaxf(f, 0.f);
-            }
-            elem<T>::store(y + o, f);
-            ++o;
-            if (++q == a.PQ) {
-              q = 0;
-              o += next_img;
-            }
-          }
-        }
       }
     }
   }
