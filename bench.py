@@ -126,10 +126,13 @@ KERNEL_SOURCES = {
     "implicit_rows_kernel": ("implicit_rows.hip", "igemm_common.hpp"),
     "conv3x3_kernel": ("conv3x3.hip", "igemm_common.hpp"),
     "implicit_ws_kernel": ("implicit_ws.hip", "igemm_common.hpp"),
-    "gemm_nt_kernel": ("gemm.hip",),
+    "gemm_": ("gemm.hip", "igemm_common.hpp"),
+    "nhwc_": ("nhwc.hip", "igemm_common.hpp"),
+    "to_nhwc_kernel": ("nhwc.hip", "igemm_common.hpp"),
+    "dw3_nhwc_kernel": ("nhwc.hip", "igemm_common.hpp"),
     "direct_": ("direct.hip",),
     "wino_": ("winograd.hip", "gemm.hip"),
-    "im2col_kernel": ("im2col.hip",),
+    "im2col_": ("im2col.hip",),
 }
 
 

@@ -247,6 +247,45 @@ conv_status_t from_hip(hipError_t e) {
   return CONV_ERR_DEVICE;
 }
 
+// The product of IM2COL + GEMM for cnt images (y: their planes).
+convsel::GemmArgs im2col_product(const Shape& s, int64_t cnt, const void* filt, const void* col, const void* b,
+                                 void* y) {
+  const int64_t crs = s.Cg * s.R * s.S, PQ = s.P * s.Q;
+  convsel::GemmArgs g;
+  g.A = filt;
+  g.B = col;
+  g.C = y;
+  g.bias = b;
+  g.M = (int)s.Kg; g.N = (int)PQ; g.Kred = (int)crs;
+  g.lda = crs; g.ldb = crs; g.ldc = PQ;
+  g.batch = (int)(cnt * s.G); g.bdiv = s.G;
+  g.sA0 = 0; g.sA1 = s.Kg * crs;                 // group g's filters
+  g.sB0 = s.G * PQ * crs; g.sB1 = PQ * crs;      // image, group rows of col
+  g.sC0 = s.K * PQ; g.sC1 = s.Kg * PQ;           // image, group planes of y
+  g.sBias1 = s.Kg;                               // group g's biases
+  g.relu = s.relu ? 1 : 0;
+  g.out_f32 = 0;
+  g.b_kmajor = 0;
+  return g;
+}
+
+// The 16 products of Winograd over Tc tiles.
+convsel::GemmArgs wino_product(const Shape& s, int64_t Tc, const void* U, const void* V, float* M) {
+  convsel::GemmArgs g;
+  g.A = U; g.B = V; g.C = M; g.bias = nullptr;
+  g.M = (int)s.K; g.N = (int)Tc; g.Kred = (int)s.C;
+  g.lda = s.C; g.ldb = s.C; g.ldc = Tc;
+  g.batch = 16; g.bdiv = 1;
+  g.sA0 = s.K * s.C; g.sA1 = 0;
+  g.sB0 = Tc * s.C; g.sB1 = 0;
+  g.sC0 = s.K * Tc; g.sC1 = 0;
+  g.sBias1 = 0;
+  g.relu = 0;
+  g.out_f32 = 1;
+  g.b_kmajor = 0;
+  return g;
+}
+
 // Runs the algorithm.  `wpk` is the filter package of conv2d_pack_filters()
 // (prepacked calls) or NULL, in which case the package is built in the
 // workspace first (implicit GEMM, Winograd) or the filters are used as they
@@ -263,27 +302,12 @@ conv_status_t run(const Shape& s, conv_algo_t algo, const void* x, const void* w
       return from_hip(launch_implicit_gemm(s, x, w, b, y, ws, st));
     case CONV_ALGO_IM2COL_GEMM: {
       const int64_t nb = im2col_batch(s, nullptr);
-      const int64_t crs = s.Cg * s.R * s.S, PQ = s.P * s.Q;
       for (int64_t n0 = 0; n0 < s.N; n0 += nb) {
         const int64_t cnt = s.N - n0 < nb ? s.N - n0 : nb;
         hipError_t e = launch_im2col(s, x, ws, n0, cnt, st);
         if (e != hipSuccess) return from_hip(e);
-        GemmArgs g;
-        g.A = filt;
-        g.B = ws;
-        g.C = (char*)y + (size_t)n0 * s.K * PQ * s.esize();
-        g.bias = b;
-        g.M = (int)s.Kg; g.N = (int)PQ; g.Kred = (int)crs;
-        g.lda = crs; g.ldb = crs; g.ldc = PQ;
-        g.batch = (int)(cnt * s.G); g.bdiv = s.G;
-        g.sA0 = 0; g.sA1 = s.Kg * crs;                 // group g's filters
-        g.sB0 = s.G * PQ * crs; g.sB1 = PQ * crs;      // image, group rows of col
-        g.sC0 = s.K * PQ; g.sC1 = s.Kg * PQ;           // image, group planes of y
-        g.sBias1 = s.Kg;                               // group g's biases
-        g.relu = s.relu ? 1 : 0;
-        g.out_f32 = 0;
-        g.b_kmajor = 0;
-        e = launch_gemm_nt(s.dtype, g, st);
+        char* out = (char*)y + (size_t)n0 * s.K * s.P * s.Q * s.esize();
+        e = launch_gemm_nt(s.dtype, im2col_product(s, cnt, filt, ws, b, out), st);
         if (e != hipSuccess) return from_hip(e);
       }
       return CONV_OK;
@@ -304,19 +328,7 @@ conv_status_t run(const Shape& s, conv_algo_t algo, const void* x, const void* w
         const int64_t Tc = cnt * L.TPQ;
         hipError_t e = launch_wino_input(s, x, V, n0, cnt, st);
         if (e != hipSuccess) return from_hip(e);
-        GemmArgs g;
-        g.A = U; g.B = V; g.C = M; g.bias = nullptr;
-        g.M = (int)s.K; g.N = (int)Tc; g.Kred = (int)s.C;
-        g.lda = s.C; g.ldb = s.C; g.ldc = Tc;
-        g.batch = 16; g.bdiv = 1;
-        g.sA0 = s.K * s.C; g.sA1 = 0;
-        g.sB0 = Tc * s.C; g.sB1 = 0;
-        g.sC0 = s.K * Tc; g.sC1 = 0;
-        g.sBias1 = 0;
-        g.relu = 0;
-        g.out_f32 = 1;
-        g.b_kmajor = 0;
-        e = launch_gemm_nt(s.dtype, g, st);
+        e = launch_gemm_nt(s.dtype, wino_product(s, Tc, U, V, M), st);
         if (e != hipSuccess) return from_hip(e);
         e = launch_wino_output(s, M, b, (char*)y + (size_t)n0 * s.K * s.P * s.Q * s.esize(), 0, cnt, st);
         if (e != hipSuccess) return from_hip(e);
@@ -548,13 +560,16 @@ conv_status_t conv2d_describe(const conv2d_desc_t* desc, conv_algo_t algo, char*
       break;
     case CONV_ALGO_IM2COL_GEMM: {
       const int64_t nb = im2col_batch(s, nullptr);
-      d = "im2col_gemm kernels=im2col_kernel;gemm_nt_kernel images_per_batch=" + std::to_string(nb);
+      d = std::string("im2col_gemm kernels=") + convsel::im2col_describe(s, nb) + ";" +
+          convsel::gemm_describe(s.dtype, im2col_product(s, nb, nullptr, nullptr, nullptr, nullptr)) +
+          " images_per_batch=" + std::to_string(nb);
       break;
     }
     case CONV_ALGO_WINOGRAD: {
       const WinoLayout L = wino_layout(s, true);
-      d = "winograd kernels=wino_filter_kernel;wino_input_kernel;gemm_nt_kernel;wino_output_kernel "
-          "images_per_batch=" + std::to_string(L.nb);
+      d = "winograd kernels=wino_filter_kernel;wino_input_kernel;" +
+          convsel::gemm_describe(s.dtype, wino_product(s, L.nb * L.TPQ, nullptr, nullptr, nullptr)) +
+          ";wino_output_kernel images_per_batch=" + std::to_string(L.nb);
       break;
     }
     case CONV_ALGO_IMPLICIT_PRECOMP_GEMM:

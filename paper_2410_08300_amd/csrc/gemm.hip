@@ -13,6 +13,10 @@
 // an 80-byte row stride, an odd multiple of 16 bytes, so the per-lane 16-byte
 // fragment reads of 32 consecutive rows hit distinct bank groups).  The next
 // k-tile is fetched into registers while the MFMAs run on the current one.
+#include <stdio.h>
+
+#include <string>
+
 #include "common.hpp"
 #include "igemm_common.hpp"
 #include "kernels.hpp"
@@ -223,7 +227,7 @@ struct GemmDmaShape {
   static constexpr int MJ = TJ / WJ / 32, NI = TI / WI / 32;  // 32 x 32 blocks per wave
   static constexpr int ROWS = TJ + TI;
   static constexpr int STAGE = ROWS * 128;
-    static constexpr int NST = NST_;
+  static constexpr int NST = NST_;
   static constexpr int NDMA = ROWS / 8 / 4;  // DMA instructions per wave and stage
   static_assert(WJ * WI == 4 && MJ >= 1 && NI >= 1 && TJ % 32 == 0 && TI % 32 == 0 && ROWS % 32 == 0, "tile");
   static_assert(NST * STAGE <= 160 * 1024 && NDMA * (NST - 1) <= 63, "stages");
@@ -438,6 +442,13 @@ bool gemm_dma_ok(int dtype, const GemmArgs& g, uint32_t& a_bytes, uint32_t& b_by
   return true;
 }
 
+// Tiles of the DMA kernel (GemmDmaShape).
+struct DmaTile {
+  int TJ, TI, WJ, NST;
+};
+constexpr DmaTile kDmaTiles[] = {{128, 256, 1, 3}, {128, 128, 2, 3}, {256, 64, 4, 3},
+                                 {128, 64, 2, 2},  {64, 64, 2, 2},   {64, 64, 2, 4}};
+
 // Tile (TJ x TI) choice.  fp32: 64 x 64, whose five workgroups per CU keep the
 // matrix units (a sixteenth of the bf16 rate) fed at any size (VGG block, two
 // layers: 313 us against 322 to 383 with the larger tiles).  bf16: the largest
@@ -446,18 +457,35 @@ bool gemm_dma_ok(int dtype, const GemmArgs& g, uint32_t& a_bytes, uint32_t& b_by
 // would share a CU at two either, and the k-tiles in flight are what hides
 // their latency: 23 filters, 2350 pixels, 2160 terms, whole call 29 us with four
 // stages, 35 with two; 48 filters, 20000 pixels, 288 terms 19 and 21).
-template <typename T, bool OUT_F32>
-hipError_t launch_dma(const GemmArgs& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t stream) {
+int dma_tile(int dtype, const GemmArgs& g) {
   auto wgs = [&](int tj, int ti) { return (int64_t)((g.N + tj - 1) / tj) * ((g.M + ti - 1) / ti) * g.batch; };
   const int mr = (g.M + 63) / 64 * 64;
-  if constexpr (sizeof(T) == 2) {
-    if (mr >= 256 && wgs(128, 256) >= 240) return launch_dma_tile<T, 128, 256, 1, 3, OUT_F32>(g, a_bytes, b_bytes, stream);
-    if (mr >= 128 && wgs(128, 128) >= 240) return launch_dma_tile<T, 128, 128, 2, 3, OUT_F32>(g, a_bytes, b_bytes, stream);
-    if (wgs(256, 64) >= 240) return launch_dma_tile<T, 256, 64, 4, 3, OUT_F32>(g, a_bytes, b_bytes, stream);
-    if (wgs(128, 64) >= 240) return launch_dma_tile<T, 128, 64, 2, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
+  if (dtype == DT_BF16) {
+    if (mr >= 256 && wgs(128, 256) >= 240) return 0;
+    if (mr >= 128 && wgs(128, 128) >= 240) return 1;
+    if (wgs(256, 64) >= 240) return 2;
+    if (wgs(128, 64) >= 240) return 3;
   }
-  if (wgs(64, 64) > 512) return launch_dma_tile<T, 64, 64, 2, 2, OUT_F32>(g, a_bytes, b_bytes, stream);
-  return launch_dma_tile<T, 64, 64, 2, 4, OUT_F32>(g, a_bytes, b_bytes, stream);
+  return wgs(64, 64) > 512 ? 4 : 5;
+}
+
+template <typename T, bool OUT_F32, int I>
+hipError_t launch_dma_config(const GemmArgs& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t stream) {
+  constexpr DmaTile t = kDmaTiles[I];
+  return launch_dma_tile<T, t.TJ, t.TI, t.WJ, t.NST, OUT_F32>(g, a_bytes, b_bytes, stream);
+}
+
+template <typename T, bool OUT_F32>
+hipError_t launch_dma(int tile, const GemmArgs& g, uint32_t a_bytes, uint32_t b_bytes, hipStream_t stream) {
+  if (tile == 4) return launch_dma_config<T, OUT_F32, 4>(g, a_bytes, b_bytes, stream);
+  if (tile == 5) return launch_dma_config<T, OUT_F32, 5>(g, a_bytes, b_bytes, stream);
+  if constexpr (sizeof(T) == 2) {
+    if (tile == 0) return launch_dma_config<T, OUT_F32, 0>(g, a_bytes, b_bytes, stream);
+    if (tile == 1) return launch_dma_config<T, OUT_F32, 1>(g, a_bytes, b_bytes, stream);
+    if (tile == 2) return launch_dma_config<T, OUT_F32, 2>(g, a_bytes, b_bytes, stream);
+    if (tile == 3) return launch_dma_config<T, OUT_F32, 3>(g, a_bytes, b_bytes, stream);
+  }
+  return hipErrorInvalidValue;
 }
 
 template <typename T, int BM, int BN, bool OUT_F32, bool BKM>
@@ -490,14 +518,13 @@ hipError_t launch_typed(const GemmArgs& g, hipStream_t stream) {
   return launch_tile<T, 128, 128, OUT_F32, false>(g, vec, stream);
 }
 
-}  // namespace
-
-hipError_t launch_gemm_nt(int dtype, const GemmArgs& g, hipStream_t stream) {
-  uint32_t ab = 0, bb = 0;
+// How a product runs: the tile of the DMA kernel, or -1 for the register-staged
+// one; `f` receives the arguments for the former.
+int gemm_route(int dtype, const GemmArgs& g, GemmArgs& f, uint32_t& a_bytes, uint32_t& b_bytes) {
   // A batch that shares A and whose B items are consecutive rows is folded
   // into N when the items are narrow (IM2COL's small planes), so that the
   // tiles are full and the grid holds enough workgroups.
-  GemmArgs f = g;
+  f = g;
   if (g.batch > 1 && g.bdiv == 1 && g.sA0 == 0 && g.sB0 == (int64_t)g.N * g.ldb && g.N < 1024 &&
       (int64_t)g.N * g.batch < ((int64_t)1 << 31)) {
     f.jspan = g.N;
@@ -506,12 +533,36 @@ hipError_t launch_gemm_nt(int dtype, const GemmArgs& g, hipStream_t stream) {
     f.batch = 1;
     f.sB0 = f.sC0 = 0;
   }
-  if (gemm_dma_ok(dtype, f, ab, bb)) {
-    if (dtype == DT_F32) return launch_dma<float, true>(f, ab, bb, stream);
-    return f.out_f32 ? launch_dma<bf16_t, true>(f, ab, bb, stream) : launch_dma<bf16_t, false>(f, ab, bb, stream);
+  return gemm_dma_ok(dtype, f, a_bytes, b_bytes) ? dma_tile(dtype, f) : -1;
+}
+
+}  // namespace
+
+hipError_t launch_gemm_nt(int dtype, const GemmArgs& g, hipStream_t stream) {
+  uint32_t ab = 0, bb = 0;
+  GemmArgs f;
+  const int tile = gemm_route(dtype, g, f, ab, bb);
+  if (tile >= 0) {
+    if (dtype == DT_F32) return launch_dma<float, true>(tile, f, ab, bb, stream);
+    return f.out_f32 ? launch_dma<bf16_t, true>(tile, f, ab, bb, stream)
+                     : launch_dma<bf16_t, false>(tile, f, ab, bb, stream);
   }
   if (dtype == DT_F32) return launch_typed<float, true>(g, stream);
   return g.out_f32 ? launch_typed<bf16_t, true>(g, stream) : launch_typed<bf16_t, false>(g, stream);
+}
+
+std::string gemm_describe(int dtype, const GemmArgs& g) {
+  uint32_t ab = 0, bb = 0;
+  GemmArgs f;
+  const int tile = gemm_route(dtype, g, f, ab, bb);
+  const char* t = dtype == DT_F32 ? "f32" : "bf16";
+  char buf[64];
+  if (tile >= 0)
+    snprintf(buf, sizeof(buf), "gemm_dma_kernel<%s,%d,%d,%d>", t, kDmaTiles[tile].TJ, kDmaTiles[tile].TI,
+             kDmaTiles[tile].NST);
+  else
+    snprintf(buf, sizeof(buf), "gemm_nt_kernel<%s,%d,128>", t, g.M <= 64 ? 64 : 128);
+  return buf;
 }
 
 }  // namespace convsel

@@ -267,6 +267,27 @@ __global__ __launch_bounds__(256) void im2col_vec_kernel(Im2colArgs a, int64_t u
 
 }  // namespace
 
+namespace {
+
+enum Im2colKernel { IM2COL_LDS, IM2COL_VEC, IM2COL_ELEM };
+
+// The kernel for the column matrix of nb images (`aligned`: col is 16-byte
+// aligned), and its tile.
+Im2colKernel im2col_route(const Shape& s, int64_t nb, bool aligned, Im2colTile& t) {
+  const int64_t crs = s.Cg * s.R * s.S, ue = s.dtype == DT_F32 ? 4 : 8;
+  if (!aligned || crs % ue != 0) return IM2COL_ELEM;
+  // Small matrices (fewer than about 800,000 units, 13 MB) stay with the
+  // element gather below: a unit per thread fills the chip at once, where the
+  // LDS tiles are too few and pay their setup (with the GEMM, bf16, 3 x 3: one
+  // 64-channel 56 x 56 image, 3.6 MB, 12.0 us against 17.9; two of 32 channels of
+  // 100 x 100, 11.5 MB, 18.9 against 20.3; 32 of 256 channels of 14 x 14, 28.9 MB,
+  // 51 against 35).
+  if (nb * s.G * s.P * s.Q * crs / ue < 800000 || !im2col_tile(s, t)) return IM2COL_VEC;
+  return nb * s.G * t.chunks * t.ptiles * t.qtiles < ((int64_t)1 << 31) ? IM2COL_LDS : IM2COL_VEC;
+}
+
+}  // namespace
+
 hipError_t launch_im2col(const Shape& s, const void* x, void* col, int64_t n0, int64_t nb,
                          hipStream_t stream) {
   Im2colArgs a;
@@ -278,27 +299,19 @@ hipError_t launch_im2col(const Shape& s, const void* x, void* col, int64_t n0, i
   a.n0 = n0;
   a.rows = nb * s.G * s.P * s.Q;
   const int64_t crs = s.Cg * s.R * s.S;
-  // Small matrices (fewer than about 800,000 units, 13 MB) stay with the
-  // element gather below: a unit per thread fills the chip at once, where the
-  // LDS tiles are too few and pay their setup (with the GEMM, bf16, 3 x 3: one
-  // 64-channel 56 x 56 image, 3.6 MB, 12.0 us against 17.9; two of 32 channels of
-  // 100 x 100, 11.5 MB, 18.9 against 20.3; 32 of 256 channels of 14 x 14, 28.9 MB,
-  // 51 against 35).
-  const int ue = s.dtype == DT_F32 ? 4 : 8;
   Im2colTile t;
-  if (a.rows * crs / ue >= 800000 && reinterpret_cast<uintptr_t>(col) % 16 == 0 && im2col_tile(s, t)) {
+  const Im2colKernel kernel = im2col_route(s, nb, reinterpret_cast<uintptr_t>(col) % 16 == 0, t);
+  if (kernel == IM2COL_LDS) {
     const int64_t blocks = nb * s.G * t.chunks * t.ptiles * t.qtiles;
     const size_t lds = (size_t)t.CC * t.plane * s.esize();
-    if (blocks < ((int64_t)1 << 31)) {
-      if (s.dtype == DT_F32)
-        hipLaunchKernelGGL(im2col_lds_kernel<float>, dim3((unsigned)blocks), dim3(256), lds, stream, a, t);
-      else
-        hipLaunchKernelGGL(im2col_lds_kernel<bf16_t>, dim3((unsigned)blocks), dim3(256), lds, stream, a, t);
-      return hipGetLastError();
-    }
+    if (s.dtype == DT_F32)
+      hipLaunchKernelGGL(im2col_lds_kernel<float>, dim3((unsigned)blocks), dim3(256), lds, stream, a, t);
+    else
+      hipLaunchKernelGGL(im2col_lds_kernel<bf16_t>, dim3((unsigned)blocks), dim3(256), lds, stream, a, t);
+    return hipGetLastError();
   }
-  if (crs % ue == 0 && reinterpret_cast<uintptr_t>(col) % 16 == 0) {
-    const int64_t units = a.rows * (crs / ue);
+  if (kernel == IM2COL_VEC) {
+    const int64_t units = a.rows * (crs * s.esize() / 16);
     const int64_t blocks = std::min<int64_t>((units + 255) / 256, 65536);
     if (s.dtype == DT_F32)
       hipLaunchKernelGGL(im2col_vec_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, stream, a, units);
@@ -313,6 +326,12 @@ hipError_t launch_im2col(const Shape& s, const void* x, void* col, int64_t n0, i
   else
     hipLaunchKernelGGL(im2col_kernel<bf16_t>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
   return hipGetLastError();
+}
+
+const char* im2col_describe(const Shape& s, int64_t nb) {
+  Im2colTile t;
+  static const char* const names[] = {"im2col_lds_kernel", "im2col_vec_kernel", "im2col_kernel"};
+  return names[im2col_route(s, nb, true, t)];
 }
 
 }  // namespace convsel

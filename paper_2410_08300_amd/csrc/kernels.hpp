@@ -50,6 +50,7 @@ struct GemmArgs {
 };
 
 hipError_t launch_gemm_nt(int dtype, const GemmArgs& g, hipStream_t stream);
+std::string gemm_describe(int dtype, const GemmArgs& g);  // the kernel that runs it
 
 // Byte copy of `bytes` from src to dst (dst 16-byte aligned).
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t stream);
@@ -175,6 +176,7 @@ std::string smm_describe(const Shape& s);
 // Column matrix [nb][G][P*Q][Cg*R*S] of images n0 .. n0+nb-1.
 hipError_t launch_im2col(const Shape& s, const void* x, void* col, int64_t n0, int64_t nb,
                          hipStream_t stream);
+const char* im2col_describe(const Shape& s, int64_t nb);  // the kernel for nb images
 
 // Winograd F(2x2,3x3) pieces.  U: 16 x K x C.  V: 16 x Tc x C and M: 16 x K x Tc
 // (fp32) for the Tc = nb*TP*TQ tiles of images n0 .. n0+nb-1.

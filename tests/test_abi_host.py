@@ -363,3 +363,20 @@ def test_static_scratch_rejects_layers_beyond_its_capacity_before_any_device_cal
     assert _lib.conv2d_static_scratch_raw(fake, fake * 2, None, fake * 3, big, algo, None) == _lib.CONV_ERR_WORKSPACE
     empty = _lib.make_desc(0, 4, 8, 8, 4, 3, 3, 1, 1)
     assert _lib.conv2d_static_scratch_raw(None, None, None, None, empty, "direct", None) == _lib.CONV_OK
+
+
+@pytest.mark.parametrize("shape,dtype,algo,kernels", [
+    # n, c, h, k, r, groups: the column matrix by LDS tiles, by 16-byte units or by elements; either product kernel
+    ((32, 128, 28, 128, 3, 1), "bf16", "im2col_gemm", "im2col_lds_kernel;gemm_dma_kernel<bf16,128,64,2>"),
+    ((1, 128, 28, 128, 3, 1), "bf16", "im2col_gemm", "im2col_vec_kernel;gemm_dma_kernel<bf16,64,64,4>"),
+    ((4, 3, 32, 40, 3, 1), "f32", "im2col_gemm", "im2col_kernel;gemm_nt_kernel<f32,64,128>"),
+    ((4, 3, 32, 80, 3, 1), "bf16", "im2col_gemm", "im2col_kernel;gemm_nt_kernel<bf16,128,128>"),
+    ((8, 256, 56, 256, 3, 1), "f32", "winograd",
+     "wino_filter_kernel;wino_input_kernel;gemm_dma_kernel<f32,64,64,2>;wino_output_kernel"),
+    ((2, 12, 20, 40, 3, 1), "bf16", "winograd",
+     "wino_filter_kernel;wino_input_kernel;gemm_nt_kernel<bf16,64,128>;wino_output_kernel"),
+], ids=str)
+def test_describe_names_the_kernels_that_run(shape, dtype, algo, kernels):
+    n, c, h, k, r, g = shape
+    d = _lib.describe(_lib.make_desc(n, c, h, h, k, r, r, 1, r // 2, 1, g, dtype), algo)
+    assert d.split("kernels=")[1].split(" ")[0] == kernels
