@@ -219,9 +219,8 @@ bool im2col_tile(const Shape& s, Im2colTile& t) {
   return true;
 }
 
-// The same matrix for the remaining layers whose rows are whole units (small
-// matrices; input rows too long, by dilation, for the LDS tile; very large
-// filters): one thread per 16-byte unit of a row, consecutive threads along the row; the UE
+// The same matrix for the remaining layers whose rows are whole units
+// (im2col_route): one thread per 16-byte unit of a row, consecutive threads along the row; the UE
 // input elements are gathered with the tap indices stepped incrementally.
 template <typename T>
 __global__ __launch_bounds__(256) void im2col_vec_kernel(Im2colArgs a, int64_t units) {
@@ -276,14 +275,26 @@ enum Im2colKernel { IM2COL_LDS, IM2COL_VEC, IM2COL_ELEM };
 Im2colKernel im2col_route(const Shape& s, int64_t nb, bool aligned, Im2colTile& t) {
   const int64_t crs = s.Cg * s.R * s.S, ue = s.dtype == DT_F32 ? 4 : 8;
   if (!aligned || crs % ue != 0) return IM2COL_ELEM;
-  // Small matrices (fewer than about 800,000 units, 13 MB) stay with the
-  // element gather below: a unit per thread fills the chip at once, where the
-  // LDS tiles are too few and pay their setup (with the GEMM, bf16, 3 x 3: one
-  // 64-channel 56 x 56 image, 3.6 MB, 12.0 us against 17.9; two of 32 channels of
-  // 100 x 100, 11.5 MB, 18.9 against 20.3; 32 of 256 channels of 14 x 14, 28.9 MB,
-  // 51 against 35).
-  if (nb * s.G * s.P * s.Q * crs / ue < 800000 || !im2col_tile(s, t)) return IM2COL_VEC;
-  return nb * s.G * t.chunks * t.ptiles * t.qtiles < ((int64_t)1 << 31) ? IM2COL_LDS : IM2COL_VEC;
+  const int64_t units = nb * s.G * s.P * s.Q * crs / ue;
+  if (s.R * s.S == 1 || !im2col_tile(s, t)) return IM2COL_VEC;
+  // Where the LDS tiles pay (the gather alone, 400 random layers, both ways):
+  //  * not for single taps, which read every element once: 0.5 times as fast at
+  //    best, and a hundredth on 1 x 1 planes;
+  //  * with 750 units for a workgroup to write on average, which its setup and
+  //    its staging round trip are spread over (fewer on small planes or with few
+  //    channels: 92 channels a group of 2 x 2, 3 x 3 taps, 24.5 us by units,
+  //    52.0 by tiles; 4 a group of 3 x 3, 17.9 and 121);
+  //  * not for filters one column wide over single output rows, whose tiles
+  //    hold no pixel twice (7 x 1, 320 channels of 71 x 71, 25 and 40 us);
+  //  * with enough units in all (13 MB in bf16, 19 MB in fp32, whose units cost
+  //    the other kernel half as many loads): below, a unit per thread fills
+  //    the chip at once (one 64-channel 56 x 56 image, bf16, 3 x 3, with its product
+  //    12.0 us by units, 17.9 by tiles; 12 channels of 78 x 78, fp32, 9.2 and 10.2).
+  // Above these lines the tiles took 0.26 to 1.1 times as long, median 0.6.
+  const int64_t blocks = nb * s.G * t.chunks * t.ptiles * t.qtiles;
+  const bool once = s.S == 1 && t.IR * t.IC * 20 > t.PR * t.QT * s.R * 17;
+  if (units < (s.dtype == DT_F32 ? 1200000 : 800000) || units < 750 * blocks || once) return IM2COL_VEC;
+  return blocks < ((int64_t)1 << 31) ? IM2COL_LDS : IM2COL_VEC;
 }
 
 }  // namespace

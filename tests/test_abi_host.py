@@ -380,3 +380,24 @@ def test_describe_names_the_kernels_that_run(shape, dtype, algo, kernels):
     n, c, h, k, r, g = shape
     d = _lib.describe(_lib.make_desc(n, c, h, h, k, r, r, 1, r // 2, 1, g, dtype), algo)
     assert d.split("kernels=")[1].split(" ")[0] == kernels
+
+
+# n, c, h, w, r, s, stride, groups
+@pytest.mark.parametrize("case,dtype,kernel", [
+    ((4000, 672, 2, 2, 1, 1, 1, 4), "f32", "im2col_vec_kernel"),     # single taps
+    ((32, 256, 56, 56, 1, 1, 1, 1), "bf16", "im2col_vec_kernel"),
+    ((2718, 184, 2, 2, 3, 3, 1, 1), "bf16", "im2col_vec_kernel"),    # few pixels a tile
+    ((6339, 16, 6, 6, 3, 3, 2, 4), "f32", "im2col_vec_kernel"),
+    ((37, 8, 90, 90, 3, 3, 1, 1), "bf16", "im2col_vec_kernel"),      # few channels
+    ((14, 320, 71, 71, 7, 1, 1, 4), "bf16", "im2col_vec_kernel"),    # no pixel staged for two taps
+    ((16, 64, 28, 28, 3, 3, 1, 1), "f32", "im2col_lds_kernel"),
+    ((10, 64, 28, 28, 3, 3, 1, 1), "f32", "im2col_vec_kernel"),      # small
+    ((32, 128, 28, 28, 3, 3, 1, 1), "bf16", "im2col_lds_kernel"),
+    ((600, 104, 7, 7, 5, 5, 2, 1), "bf16", "im2col_lds_kernel"),
+    ((1 << 24, 8, 1, 1, 1, 1, 1, 1), "bf16", "im2col_vec_kernel"),   # a workgroup a pixel would exceed a launch
+], ids=str)
+def test_im2col_kernel_choice(case, dtype, kernel):
+    n, c, h, w, r, s, stride, g = case
+    pad = (0, 0) if r == s == 1 else (r // 2, s // 2)
+    desc = _lib.make_desc(n, c, h, w, 8 * g, r, s, stride, pad, 1, g, dtype)
+    assert "kernels=%s;" % kernel in _lib.describe(desc, "im2col_gemm")

@@ -15,16 +15,18 @@ DEV = torch.device("cuda:0")
 TDT = {"f32": torch.float32, "bf16": torch.bfloat16}
 
 
-# N, C, H, W, R, S, stride, pad, dilation, groups.  The LDS gather (800,000 16-byte units and more) has tiles of 64
-# output columns and 64 (bf16) or 32 (fp32) channels; small matrices, rows that are no whole units and very long or
-# wide filters keep the other two.
+# N, C, H, W, R, S, stride, pad, dilation, groups.  The LDS gather (large matrices, several taps) has tiles of 64
+# output columns and 64 (bf16) or 32 (fp32) channels; small matrices, small tiles, rows that are no whole units and
+# very long or wide filters keep the other two.
 IM2COL = [
     (200, 64, 9, 65, 3, 3, 1, 1, 1, 1),        # one column past a column tile
     (180, 72, 9, 64, 3, 3, 1, 1, 1, 1),         # channel remainder of 8, one full column tile
     (2400, 200, 7, 7, 3, 3, 2, 1, 1, 2),       # groups with a channel remainder, stride 2
-    (2100, 8, 130, 3, 1, 1, 1, 0, 1, 1),       # one tap, narrow rows
-    (13000, 512, 1, 1, 1, 1, 1, 0, 1, 1),       # one pixel: one staged row and column
+    (2100, 8, 130, 3, 1, 1, 1, 0, 1, 1),       # one tap, narrow rows: 16-byte units
+    (13000, 512, 1, 1, 1, 1, 1, 0, 1, 1),       # one pixel
     (110, 96, 13, 150, 5, 3, (1, 2), (2, 1), 1, 1),  # mixed strides, 75 columns
+    (2000, 92, 5, 5, 3, 3, 1, 1, 1, 1),        # whole small planes, channel remainder
+    (2600, 112, 6, 4, 5, 5, (2, 1), 2, 1, 1),  # 12 pixels a tile
     (150, 16, 20, 21, 7, 7, 1, 3, 1, 1),       # 49 taps: smaller channel chunks
     (3, 8, 40, 40, 17, 17, 1, 8, 1, 1),        # 289 units per pixel: the general vector gather
     (1, 16, 150, 150, 3, 3, 1, 60, 60, 1),     # dilation 60: tiles halved until they fit, or the vector gather
