@@ -449,24 +449,49 @@ struct DmaTile {
 constexpr DmaTile kDmaTiles[] = {{128, 256, 1, 3}, {128, 128, 2, 3}, {256, 64, 4, 3},
                                  {128, 64, 2, 2},  {64, 64, 2, 2},   {64, 64, 2, 4}};
 
+int64_t tiles_of(const GemmArgs& g, int tj, int ti) {
+  return (int64_t)((g.N + tj - 1) / tj) * ((g.M + ti - 1) / ti) * g.batch;
+}
+
 // Tile (TJ x TI) choice.  fp32: 64 x 64, whose five workgroups per CU keep the
 // matrix units (a sixteenth of the bf16 rate) fed at any size (VGG block, two
-// layers: 313 us against 322 to 383 with the larger tiles).  bf16: the largest
-// tile whose grid fills the CUs, with TI no wider than M needs; small problems
-// take the 64 x 64 tile, and up to two workgroups per CU four stages (no more
-// would share a CU at two either, and the k-tiles in flight are what hides
-// their latency: 23 filters, 2350 pixels, 2160 terms, whole call 29 us with four
-// stages, 35 with two; 48 filters, 20000 pixels, 288 terms 19 and 21).
+// layers: 313 us against 322 to 383 with the larger tiles).  bf16 with at most
+// 512 terms and more than two 64 x 64 tiles per CU takes those as well, several
+// workgroups per CU hiding each other's start and end (504 random products: 0.81
+// to 0.98 of the time with the larger tiles, at worst 1.06); longer reductions
+// the largest tile whose grid fills the CUs, with TI no wider than M needs.
+// Small problems take the 64 x 64 tile, and up to two workgroups per CU four
+// stages (no more would share a CU at two either, and the k-tiles in flight are
+// what hides their latency: 23 filters, 2350 pixels, 2160 terms, whole call 29 us
+// with four stages, 35 with two; 48 filters, 20000 pixels, 288 terms 19 and 21).
 int dma_tile(int dtype, const GemmArgs& g) {
-  auto wgs = [&](int tj, int ti) { return (int64_t)((g.N + tj - 1) / tj) * ((g.M + ti - 1) / ti) * g.batch; };
   const int mr = (g.M + 63) / 64 * 64;
-  if (dtype == DT_BF16) {
-    if (mr >= 256 && wgs(128, 256) >= 240) return 0;
-    if (mr >= 128 && wgs(128, 128) >= 240) return 1;
-    if (wgs(256, 64) >= 240) return 2;
-    if (wgs(128, 64) >= 240) return 3;
+  if (dtype == DT_BF16 && (g.Kred > 512 || tiles_of(g, 64, 64) <= 512)) {
+    if (mr >= 256 && tiles_of(g, 128, 256) >= 240) return 0;
+    if (mr >= 128 && tiles_of(g, 128, 128) >= 240) return 1;
+    if (tiles_of(g, 256, 64) >= 240) return 2;
+    if (tiles_of(g, 128, 64) >= 240) return 3;
   }
-  return wgs(64, 64) > 512 ? 4 : 5;
+  return tiles_of(g, 64, 64) > 512 ? 4 : 5;
+}
+
+// Products that the register-staged kernel runs faster than the DMA kernel:
+// those bound by their stores.  A lane of the DMA kernel ends with four
+// consecutive columns of a row, 32 rows a wave, which is four scattered stores
+// instead of one where rows of C are no whole 16-byte units; its own lanes run
+// along the rows.  With grids of several workgroups per CU and rows long enough
+// for its 128 columns (1176 random products, both ways, fp32 and bf16): such rows
+// up to 256 terms 0.5 to 1.0 of the DMA kernel's time (16 -> 106 channels of 62 x 62,
+// Winograd, 17 images, fp32: 60 us against 113), up to 16 terms on any large grid;
+// rows of whole units up to 32 terms 0.7 to 1.05.  Not folded batches, whose items
+// it would take one by one.
+bool stores_bound(const GemmArgs& f) {
+  if (f.jspan > 0) return false;
+  const bool whole = f.ldc % 4 == 0 && f.sC0 % 4 == 0 && f.sC1 % 4 == 0 &&
+                     reinterpret_cast<uintptr_t>(f.C) % 16 == 0;
+  const int64_t tiles = tiles_of(f, 64, 64);
+  if (whole) return f.N > 1500 && tiles > 1024 && f.Kred <= 32;
+  return (f.N > 1500 && tiles > 800 && f.Kred <= 256) || (tiles > 512 && f.Kred <= 16);
 }
 
 template <typename T, bool OUT_F32, int I>
@@ -533,7 +558,7 @@ int gemm_route(int dtype, const GemmArgs& g, GemmArgs& f, uint32_t& a_bytes, uin
     f.batch = 1;
     f.sB0 = f.sC0 = 0;
   }
-  return gemm_dma_ok(dtype, f, a_bytes, b_bytes) ? dma_tile(dtype, f) : -1;
+  return gemm_dma_ok(dtype, f, a_bytes, b_bytes) && !stores_bound(f) ? dma_tile(dtype, f) : -1;
 }
 
 }  // namespace

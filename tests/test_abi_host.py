@@ -401,3 +401,23 @@ def test_im2col_kernel_choice(case, dtype, kernel):
     pad = (0, 0) if r == s == 1 else (r // 2, s // 2)
     desc = _lib.make_desc(n, c, h, w, 8 * g, r, s, stride, pad, 1, g, dtype)
     assert "kernels=%s;" % kernel in _lib.describe(desc, "im2col_gemm")
+
+
+# n, c, h, k, r: products by the kernel whose stores run along the rows, or by DMA
+@pytest.mark.parametrize("case,dtype,algo,kernel", [
+    ((17, 16, 62, 84, 3), "f32", "winograd", "gemm_nt_kernel<f32,128,128>"),
+    ((5, 28, 166, 222, 3), "f32", "winograd", "gemm_nt_kernel<f32,128,128>"),
+    ((4, 28, 166, 222, 3), "f32", "winograd", "gemm_nt_kernel<f32,128,128>"),
+    ((8, 256, 56, 256, 3), "f32", "winograd", "gemm_dma_kernel<f32,64,64,2>"),
+    ((9, 320, 46, 50, 3), "f32", "winograd", "gemm_dma_kernel<f32,64,64,2>"),
+    ((9, 256, 46, 50, 3), "f32", "winograd", "gemm_nt_kernel<f32,64,128>"),
+    ((16, 32, 98, 100, 1), "bf16", "im2col_gemm", "gemm_nt_kernel<bf16,128,128>"),
+    ((16, 40, 98, 100, 1), "bf16", "im2col_gemm", "gemm_dma_kernel<bf16,64,64,2>"),
+    ((16, 512, 98, 130, 1), "bf16", "im2col_gemm", "gemm_dma_kernel<bf16,64,64,2>"),
+    ((16, 520, 98, 130, 1), "bf16", "im2col_gemm", "gemm_dma_kernel<bf16,128,128,3>"),
+    ((64, 8, 29, 60, 1), "f32", "im2col_gemm", "gemm_dma_kernel<f32,64,64,2>"),     # items of 841 columns folded
+], ids=str)
+def test_product_kernel_choice(case, dtype, algo, kernel):
+    n, c, h, k, r = case
+    desc = _lib.make_desc(n, c, h, h, k, r, r, 1, r // 2, 1, 1, dtype)
+    assert ";" + kernel in _lib.describe(desc, algo)
