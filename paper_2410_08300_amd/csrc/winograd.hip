@@ -127,24 +127,41 @@ __global__ __launch_bounds__(256) void wino_input_kernel(const T* __restrict__ x
   }
 }
 
+// Workgroups along a row of TQ tiles, lpr lanes to an input row.
+int wino_row_blocks(int TQ, int lpr) { return (TQ + lpr / 2 - 2) / (lpr / 2 - 1); }
+
+// Lanes per input row.  16, seven tiles a workgroup: the most workgroups, and the
+// least LDS each (240 random inputs: within 5 percent of the best width in bf16
+// and for few channels or tiles, where 32 and 64 lanes take up to twice as
+// long: 5 channels of 54 x 54, two images, 2.7, 3.8 and 5.3 us).  In fp32, with more
+// than a block of channels and 2400 workgroups at 16 lanes, V's 128-byte rows are
+// what bounds it, and longer runs of them help: 32 lanes (219 channels of 18 x 19,
+// 26 images, 15.0 -> 12.5 us), or 64 where the row has the tiles and V (14 KB for
+// seven tiles) stays below 430 MB (297 of 46 x 47, 10 images: 58.7, 40.5 and 35.6;
+// but 343 of 56 x 56, 36 images: 279, 252 and 364).
+int wino_input_lanes(const Shape& s, int64_t nb) {
+  const int TP = (int)((s.P + 1) / 2), TQ = (int)((s.Q + 1) / 2);
+  const int64_t blocks = nb * TP * wino_row_blocks(TQ, 16) * ((s.C + CB - 1) / CB);
+  if (s.dtype != DT_F32 || s.C <= CB || blocks < 2400) return 16;
+  const bool full = 64 * wino_row_blocks(TQ, 64) * 3 <= 16 * wino_row_blocks(TQ, 16) * 4;
+  return TQ > 16 && full && blocks < 30000 ? 64 : 32;
+}
+
 template <typename T>
 void launch_wino_input_typed(const Shape& s, const void* x, void* V, int64_t n0, int64_t nb, hipStream_t stream) {
   const int TP = (int)((s.P + 1) / 2), TQ = (int)((s.Q + 1) / 2);
   const int64_t Tc = nb * TP * TQ;
-  // Lanes per input row: the width whose blocks waste the fewest lanes on a
-  // tile row (7 tiles: 16 lanes, 14: 32, 28: 64), the widest of equals.
-  int best = 64;
-  auto lanes = [&](int lpr) { return (TQ + lpr / 2 - 2) / (lpr / 2 - 1) * lpr; };
-  if (lanes(32) < lanes(best)) best = 32;
-  if (lanes(16) < lanes(best)) best = 16;
-  const dim3 grid((unsigned)(TP * (lanes(best) / best)), (unsigned)((s.C + CB - 1) / CB), (unsigned)nb);
+  const int best = wino_input_lanes(s, nb);
+  const dim3 grid((unsigned)(TP * wino_row_blocks(TQ, best)), (unsigned)((s.C + CB - 1) / CB), (unsigned)nb);
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, stream, (const T*)x, (T*)V, (int)s.C, (int)s.H, (int)s.W, s.ph, s.pw,
                        TP, TQ, n0, Tc);
   };
-  if (best == 64) go(wino_input_kernel<T, 64>);
-  else if (best == 32) go(wino_input_kernel<T, 32>);
-  else go(wino_input_kernel<T, 16>);
+  if constexpr (sizeof(T) == 4) {
+    if (best == 64) return go(wino_input_kernel<T, 64>);
+    if (best == 32) return go(wino_input_kernel<T, 32>);
+  }
+  go(wino_input_kernel<T, 16>);
 }
 
 // y tiles from M[xi*4+nu][k][t] (fp32); one thread per (k, t), t fastest.

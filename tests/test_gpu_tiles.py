@@ -64,6 +64,18 @@ def test_winograd_input_transform_tiles(tiles, dtype):
         assert np.abs(f64(V) - ref).max() <= tol * np.abs(ref).max()
 
 
+# Large fp32 inputs take 15 or 31 tiles per workgroup: tile rows one short of a block, whole, and one over, and a
+# channel remainder; 64 lanes only for rows that fill them.
+@pytest.mark.parametrize("n,c,w", [(45, 65, 28), (45, 65, 30), (45, 65, 32), (40, 70, 60), (40, 70, 62), (25, 65, 125)])
+def test_winograd_input_transform_wide_blocks(n, c, w):
+    x = torch.randn(n, c, 28, w, generator=torch.Generator().manual_seed(w))
+    say("winograd input wide blocks", n, c, w)
+    V = cs.winograd_input_transform(x.to(DEV), padding=1)
+    torch.cuda.synchronize()
+    ref = oracle.winograd_input_transform(f64(x), padding=1).reshape(16, -1, c)
+    assert np.abs(f64(V) - ref).max() <= 4 * 2.0 ** -24 * np.abs(ref).max()
+
+
 # K, C, H, W of 1x1 IM2COL + GEMM layers: the products' tiles (64 or more rows and columns, k-tiles of 64 bf16 or
 # 32 fp32) with remainders on each axis, batches folded and not (planes of 1024 pixels), and reductions that are
 # no whole 16-byte units (the register-staged kernel).
