@@ -479,19 +479,20 @@ int dma_tile(int dtype, const GemmArgs& g) {
 // those bound by their stores.  A lane of the DMA kernel ends with four
 // consecutive columns of a row, 32 rows a wave, which is four scattered stores
 // instead of one where rows of C are no whole 16-byte units; its own lanes run
-// along the rows.  With grids of several workgroups per CU and rows long enough
-// for its 128 columns (1176 random products, both ways, fp32 and bf16): such rows
-// up to 256 terms 0.5 to 1.0 of the DMA kernel's time (16 -> 106 channels of 62 x 62,
-// Winograd, 17 images, fp32: 60 us against 113), up to 16 terms on any large grid;
-// rows of whole units up to 32 terms 0.7 to 1.05.  Not folded batches, whose items
-// it would take one by one.
+// along the rows.  Where its grid (128 columns, 64 or 128 rows) fills the chip
+// (1176 random products, both ways, fp32 and bf16): such rows up to 256 terms 0.5
+// to 1.05 of the DMA kernel's time (16 -> 106 channels of 62 x 62, Winograd, 17 images,
+// fp32: 60 us against 113), up to 64 terms from 256 workgroups on, and up to 16
+// terms on any large grid; rows of whole units up to 32 terms 0.7 to 1.05.  Not
+// folded batches, whose items it would take one by one.
 bool stores_bound(const GemmArgs& f) {
   if (f.jspan > 0) return false;
   const bool whole = f.ldc % 4 == 0 && f.sC0 % 4 == 0 && f.sC1 % 4 == 0 &&
                      reinterpret_cast<uintptr_t>(f.C) % 16 == 0;
-  const int64_t tiles = tiles_of(f, 64, 64);
-  if (whole) return f.N > 1500 && tiles > 1024 && f.Kred <= 32;
-  return (f.N > 1500 && tiles > 800 && f.Kred <= 256) || (tiles > 512 && f.Kred <= 16);
+  const int64_t grid = tiles_of(f, 128, f.M <= 64 ? 64 : 128);
+  if (whole) return f.N > 1500 && grid > 512 && f.Kred <= 32;
+  if (f.N > 1200 && ((grid > 340 && f.Kred <= 256) || (grid > 256 && f.Kred <= 64))) return true;
+  return tiles_of(f, 64, 64) > 512 && f.Kred <= 16;
 }
 
 template <typename T, bool OUT_F32, int I>

@@ -406,6 +406,8 @@ def test_im2col_kernel_choice(case, dtype, kernel):
 # n, c, h, k, r: products by the kernel whose stores run along the rows, or by DMA
 @pytest.mark.parametrize("case,dtype,algo,kernel", [
     ((17, 16, 62, 84, 3), "f32", "winograd", "gemm_nt_kernel<f32,128,128>"),
+    ((5, 32, 42, 64, 3), "f32", "winograd", "gemm_nt_kernel<f32,64,128>"),
+    ((4, 32, 42, 64, 3), "f32", "winograd", "gemm_dma_kernel<f32,64,64,4>"),
     ((5, 28, 166, 222, 3), "f32", "winograd", "gemm_nt_kernel<f32,128,128>"),
     ((4, 28, 166, 222, 3), "f32", "winograd", "gemm_nt_kernel<f32,128,128>"),
     ((8, 256, 56, 256, 3), "f32", "winograd", "gemm_dma_kernel<f32,64,64,2>"),
