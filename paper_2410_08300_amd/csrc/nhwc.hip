@@ -33,7 +33,8 @@
 // Output is channels-last (OUTC: filters are the MFMA's rows, so a lane holds
 // four consecutive channels of one pixel) or N x K x P x Q (pixels are its
 // rows).  Either way the tile is rounded, staged in LDS as output rows and
-// stored, after the optional residual add, in 16-byte units along them.
+// stored, after the optional residual add, in 16-byte units along them (pixel
+// by pixel along planes that are no whole units).
 #include <stdio.h>
 
 #include <algorithm>
@@ -115,10 +116,16 @@ struct NhTile {
   static_assert((NB + NA) * (NST - 1) <= 63 && LDS <= 160 * 1024, "stages");
 };
 
+// What the output is: channels-last, planes of whole 16-byte units (bf16: or half
+// units), or planes of any size.  (A form each: with the last one in the same
+// kernel the others ran 5 percent longer.)
+enum { NH_OUT_PIXELS, NH_OUT_PLANES, NH_OUT_ODD_PLANES };
+
 // GEN: the tap is a lane's own and part of its offset; otherwise all lanes are on
 // one tap, whose offset is the DMA's scalar offset (nh_uniform_taps()).
-template <typename T, typename Tl, bool GEN, bool OUTC>
+template <typename T, typename Tl, bool GEN, int OUT>
 __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
+  constexpr bool OUTC = OUT == NH_OUT_PIXELS;
   constexpr int TJ = Tl::TJ, TI = Tl::TI, MJ = Tl::MJ, NI = Tl::NI, NB = Tl::NB, NA = Tl::NA, NST = Tl::NST;
   constexpr int ES = elem<T>::bytes, UE = elem<T>::per16, WS = Tl::WS, G = Tl::G;
   extern __shared__ __align__(16) vec16 smem[];
@@ -449,34 +456,7 @@ __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
 #pragma unroll
       for (int it = 0; it < PASSES; ++it)
         if (RPI * it < left) store16(y + o0 + it * step, d[it]);
-    } else if (a.PQ % (sizeof(T) == 2 ? 4 : UE) != 0) {
-      // Planes of no whole units: one pixel per lane, so that a wave's stores run
-      // along a channel's pixels.  (Eight pixels of a lane one after the other
-      // instead, a store's lanes 16 bytes apart: 4 -> 126 channels, 2 x 2, 55
-      // images of 47 x 47 outputs, whole layer 47.7 us, this way 24.1.)
-      constexpr int LPX = COLS < 64 ? COLS : 64, RL = 64 / LPX;  // lanes along a row, rows per pass
-      const int left = a.K - rbase - lane / LPX;
-#pragma unroll
-      for (int cb = 0; cb < COLS; cb += LPX) {
-        const int col = cb + lane % LPX, j = j0 + wj * MJ * 32 + col;
-        if (j >= a.NPQ) continue;
-        const int n = j / a.PQ;
-        const int64_t o0 = (static_cast<int64_t>(n) * a.K + rbase + lane / LPX) * a.PQ + (j - n * a.PQ);
-#pragma unroll
-        for (int it = 0; it < ROWS / RL; ++it) {
-          if (RL * it >= left) break;
-          const int row = lane / LPX + RL * it;
-          const int64_t o = o0 + static_cast<int64_t>(RL * it) * a.PQ;
-          float f = elem<T>::load(reinterpret_cast<const T*>(
-              stg + row * (U * 16) + (((col / UE) ^ (row & (U - 1))) << 4) + (col % UE) * ES));
-          if (res) {
-            f += elem<T>::load(res + o);
-            if (a.relu) f = fmaxf(f, 0.f);
-          }
-          elem<T>::store(y + o, f);
-        }
-      }
-    } else {
+    } else if constexpr (OUT == NH_OUT_PLANES) {
       // UE consecutive pixels of a channel: a whole unit of one image, or (bf16,
       // planes of whole half units) two halves.
       if (cbase >= a.NPQ) return;
@@ -525,6 +505,42 @@ __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
 #pragma unroll
           for (int h = 0; h < 2; ++h)
             if (RPI * it < left && in[h]) __builtin_memcpy(y + o[h] + it * step, &d[it].d[2 * h], 8);
+      }
+    } else {
+      // Planes of no whole units: one pixel per lane, so that a wave's stores run
+      // along a channel's pixels.  (Eight pixels of a lane one after the other
+      // instead, a store's lanes 16 bytes apart: 4 -> 126 channels, 2 x 2, 55
+      // images of 47 x 47 outputs, whole layer 47.7 us, this way 24.1.)
+      constexpr int LPX = COLS < 64 ? COLS : 64, RL = 64 / LPX;  // lanes along a row, rows per pass
+      const int left = a.K - rbase - lane / LPX;
+#pragma unroll
+      for (int cb = 0; cb < COLS; cb += LPX) {
+        const int col = cb + lane % LPX, j = j0 + wj * MJ * 32 + col;
+        if (j >= a.NPQ || left <= 0) continue;
+        const int n = j / a.PQ;
+        const int64_t o0 = (static_cast<int64_t>(n) * a.K + rbase + lane / LPX) * a.PQ + (j - n * a.PQ);
+        constexpr int BATCH = ROWS / RL < 16 ? ROWS / RL : 16;  // residuals requested together
+#pragma unroll
+        for (int it0 = 0; it0 < ROWS / RL; it0 += BATCH) {
+          T r[BATCH];
+          if (res) {
+#pragma unroll
+            for (int t = 0; t < BATCH; ++t)  // (rows past K read the first one)
+              r[t] = res[RL * (it0 + t) < left ? o0 + static_cast<int64_t>(RL * (it0 + t)) * a.PQ : o0];
+          }
+#pragma unroll
+          for (int t = 0; t < BATCH; ++t) {
+            const int row = lane / LPX + RL * (it0 + t);
+            if (RL * (it0 + t) >= left) continue;
+            float f = elem<T>::load(reinterpret_cast<const T*>(
+                stg + row * (U * 16) + (((col / UE) ^ (row & (U - 1))) << 4) + (col % UE) * ES));
+            if (res) {
+              f += elem<T>::to_f32(r[t]);
+              if (a.relu) f = fmaxf(f, 0.f);
+            }
+            elem<T>::store(y + o0 + static_cast<int64_t>(RL * (it0 + t)) * a.PQ, f);
+          }
+        }
       }
     }
   }
@@ -761,9 +777,9 @@ int nh_config(const Shape& s) {
   return best;
 }
 
-template <typename T, typename Tl, bool GEN, bool OUTC>
+template <typename T, typename Tl, bool GEN, int OUT>
 hipError_t nh_launch(const NhArgs& a, hipStream_t stream) {
-  const auto kern = nhwc_conv_kernel<T, Tl, GEN, OUTC>;
+  const auto kern = nhwc_conv_kernel<T, Tl, GEN, OUT>;
   if (Tl::LDS > 64 * 1024) {
     static std::atomic<bool> set{false};
     if (!set.load()) {
@@ -782,8 +798,11 @@ hipError_t nh_dispatch_tile(NhArgs& a, bool gen, bool outc, hipStream_t st) {
   a.njt = (a.NPQ + Tl::TJ - 1) / Tl::TJ;
   a.nit = (a.K + Tl::TI - 1) / Tl::TI;
   a.units = a.njt * a.nit;
-  if (gen) return outc ? nh_launch<T, Tl, true, true>(a, st) : nh_launch<T, Tl, true, false>(a, st);
-  return outc ? nh_launch<T, Tl, false, true>(a, st) : nh_launch<T, Tl, false, false>(a, st);
+  if (outc) return gen ? nh_launch<T, Tl, true, NH_OUT_PIXELS>(a, st) : nh_launch<T, Tl, false, NH_OUT_PIXELS>(a, st);
+  // (The tile whose waves split the steps stores pixel by pixel anyway.)
+  constexpr int ODD = Tl::WS == 1 ? NH_OUT_ODD_PLANES : NH_OUT_PLANES;
+  if (a.PQ % 4 != 0) return gen ? nh_launch<T, Tl, true, ODD>(a, st) : nh_launch<T, Tl, false, ODD>(a, st);
+  return gen ? nh_launch<T, Tl, true, NH_OUT_PLANES>(a, st) : nh_launch<T, Tl, false, NH_OUT_PLANES>(a, st);
 }
 
 template <typename T, int I>
