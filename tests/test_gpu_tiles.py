@@ -66,7 +66,7 @@ def test_winograd_input_transform_tiles(tiles, dtype):
 
 # Large fp32 inputs take 15 or 31 tiles per workgroup: tile rows one short of a block, whole, and one over, and a
 # channel remainder; 64 lanes only for rows that fill them.
-@pytest.mark.parametrize("n,c,w", [(45, 65, 28), (45, 65, 30), (45, 65, 32), (40, 70, 60), (40, 70, 62), (25, 65, 125)])
+@pytest.mark.parametrize("n,c,w", [(45, 65, 28), (45, 65, 30), (45, 65, 32), (40, 70, 60), (40, 70, 62), (25, 65, 100)])
 def test_winograd_input_transform_wide_blocks(n, c, w):
     x = torch.randn(n, c, 28, w, generator=torch.Generator().manual_seed(w))
     say("winograd input wide blocks", n, c, w)
