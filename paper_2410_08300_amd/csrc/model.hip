@@ -526,7 +526,7 @@ void plan_layouts(convsel_model& m, int out_root) {
       can[i] = op.algo_run == CONV_ALGO_IMPLICIT_GEMM && s.C % ue == 0 && s.K % ue == 0 && convsel::nhwc_applies(s);
   }
   // Candidates: storage roots, then those with an operation that cannot are
-  // struck out until nothing changes.
+  // struck out until nothing changes; then the chains that do not pay.
   std::vector<char> cl(nv, 0);
   for (int v = 1; v < nv; ++v)
     cl[v] = m.vals[v].alias < 0 && m.vals[v].falias < 0 && v != out_root && m.vals[v].ndim == 4 &&
@@ -581,26 +581,75 @@ void plan_layouts(convsel_model& m, int out_root) {
       }
     }
   }
-  // Copies have to pay.  On planes of whole 16-byte rows the N x C x H x W
-  // kernels are as fast (28 x 28 bottleneck, 32 images: 46 us, channels-last 62,
-  // of which the copy of its input 12), on others they repack planes or read
-  // pixel pairs and take up to twice the time.  So a network whose input needs
-  // a copy goes channels-last only with such planes in it, or when the copy is
-  // small (2 MB: 3 us, where the many launches of a small batch matter more).
-  int64_t copied = 0;
-  bool odd = false, depthwise = false;
+  // Chains: values that operations of the path connect, decided on one by one.
+  std::vector<int> chain(nv);
+  for (int v = 0; v < nv; ++v) chain[v] = v;
+  auto find = [&](int v) {
+    while (chain[v] != v) v = chain[v] = chain[chain[v]];
+    return v;
+  };
+  auto join = [&](int a, int b) {
+    if (cl[a] && cl[b]) chain[find(a)] = find(b);
+  };
+  for (const Op& op : m.ops) {
+    if (op.kind == OP_FLATTEN || op.skip) continue;
+    const int out = m.root(op.out);
+    join(m.root(op.in), out);
+    if (op.kind == OP_ADD) join(m.root(op.in2), out);
+    if (op.kind == OP_CONV && op.res >= 0) join(m.root(op.res), out);
+  }
+  struct Chain {
+    int64_t copied = 0;
+    bool odd = false, depthwise = false, whole_rows = false;
+    std::vector<int> copies;
+  };
+  std::vector<Chain> chains(nv);
   for (size_t i = 0; i < m.ops.size(); ++i) {
     const Op& op = m.ops[i];
     if (op.kind != OP_CONV || !can[i]) continue;
     const int in = m.root(op.in), out = m.root(op.out);
     if (!cl[in] && !cl[out]) continue;
-    depthwise = depthwise || op.shape.G > 1;
-    if (!cl[in] && !plane1(op.in)) copied += m.vals[in].elems() * m.esize();
-    odd = odd || op.shape.P * op.shape.Q % 8 != 0 || (op.shape.H * op.shape.W % 8 != 0 && op.shape.R == 1);
+    Chain& ch = chains[find(cl[in] ? in : out)];
+    ch.depthwise = ch.depthwise || (op.shape.G > 1 && (m.dtype == CONV_F32 || op.shape.W % 8 != 0));
+    ch.whole_rows = ch.whole_rows || (op.shape.G > 1 && op.shape.W % 8 == 0);
+    ch.odd = ch.odd || op.shape.P * op.shape.Q % 8 != 0 || (op.shape.H * op.shape.W % 8 != 0 && op.shape.R == 1);
+    if (!cl[in] && (!plane1(op.in) || callers(in)) &&
+        std::find(ch.copies.begin(), ch.copies.end(), in) == ch.copies.end()) {
+      ch.copies.push_back(in);
+      ch.copied += m.vals[in].elems() * m.esize();
+    }
   }
-  // fp32 chains go channels-last around depthwise layers only (an inverted block,
-  // 96 -> 576 -> 96 of 14 x 14, 64 images: 87 us, channels-last 64).
-  if (m.dtype == CONV_F32 ? !depthwise : copied > (2 << 20) && !odd && !depthwise) return;
+  // Copies have to pay.  On planes of whole 16-byte rows the N x C x H x W
+  // kernels are as fast (28 x 28 bottleneck, 32 images: 46 us, channels-last 62,
+  // of which the copy of its input 12), on others they repack planes or read
+  // pixel pairs and take up to twice the time.  So a chain whose input needs
+  // a copy goes channels-last only with such planes in it, or when the copy is
+  // small (2 MB: 3 us, where the many launches of a small batch matter more).
+  // Depthwise layers gain by themselves, in bf16 where the rows they read are no
+  // whole 16 bytes (inverted blocks: 48 of 60 x 60, 22 images, 80 us, channels-last
+  // 78; 32 of 14 x 14, 11 images, 28 and 20; but 48 of 56 x 56, 19 images, 61 and 68, and
+  // 24 of 40 x 40, 8 images, 20.5 and 21.9): a chain with whole rows only keeps its
+  // planes however small its copy.
+  // fp32 networks go channels-last, all their chains, where they have depthwise
+  // layers (96 -> 576 -> 96 of 14 x 14, 64 images, 87 us, channels-last 64; MobileNetV2
+  // at batch 1 591, with the chains around its depthwise layers alone 496, with all
+  // of them 388; three 28 x 28 bottlenecks before a depthwise block, batch 1, 173, 133, 122).
+  bool depthwise = false;
+  for (int v = 0; v < nv; ++v) depthwise = depthwise || (cl[v] && chains[find(v)].depthwise);
+  auto pays = [&](const Chain& ch) {
+    if (m.dtype == CONV_F32) return depthwise;
+    return ch.depthwise || ch.odd || (!ch.whole_rows && ch.copied <= (2 << 20));
+  };
+  bool any = false, none = true;
+  std::vector<char> keep(nv, 0);
+  for (int v = 0; v < nv; ++v) {
+    if (!cl[v]) continue;
+    none = false;
+    keep[v] = pays(chains[find(v)]);
+    any = any || keep[v];
+  }
+  cl = keep;
+  if (!any && (m.dtype == CONV_F32 || !none)) return;  // (else layers of 1 x 1 planes alone go the path)
   for (int v = 0; v < nv; ++v) m.vals[v].cl = cl[v];
   for (size_t i = 0; i < m.ops.size(); ++i) {
     Op& op = m.ops[i];

@@ -349,3 +349,66 @@ def test_variant_cases_cover_what_is_dispatched():
         seen |= variants.reached(case, m.describe())
         plans += 1
     assert len(seen) > 60 and seen <= covered, sorted(seen - covered)
+
+
+class TwoChains(nn.Module):
+    """Two pairs of convolutions with a layer between them that channels-last values do not pass."""
+
+    def __init__(self, first, second, c):
+        super().__init__()
+        self.first, self.between, self.second = first, nn.Conv2d(c, c, 3, 1, 1), second
+
+    def forward(self, x):
+        return self.second(self.between(self.first(x)))
+
+
+def _pair(c, depthwise):
+    mid = [nn.Conv2d(c, c, 3, 1, 1, groups=c)] if depthwise else []
+    return nn.Sequential(nn.Conv2d(c, c, 1), *mid, nn.Conv2d(c, c, 1))
+
+
+def _chains_of(net, shape):
+    algo = {name: "direct" if m.groups > 1 else "implicit_gemm" for name, m in net.named_modules()
+            if isinstance(m, nn.Conv2d)}
+    algo["between"] = "im2col_gemm"
+    m = cs.swap_backend(net, algo)
+    m._native.plan(*shape)
+    return ["channels_last" in line for line in m._native.describe().splitlines() if " conv " in " " + line]
+
+
+def test_layouts_are_decided_chain_by_chain():
+    """bf16: an odd plane, or a depthwise layer, decides for the convolutions it is connected to, and no others."""
+    net = TwoChains(nn.Sequential(nn.Conv2d(64, 64, 1), nn.Conv2d(64, 64, 3, 1, 1, groups=64), nn.Conv2d(64, 64, 1),
+                                  nn.MaxPool2d(3, 1)), _pair(64, False), 64).to(torch.bfloat16)
+    assert _chains_of(net, (40, 64, 58, 58)) == [True] * 3 + [False] * 3      # then 56 x 56: whole planes, large copies
+    net = TwoChains(_pair(32, True), _pair(32, False), 32)                   # float32: all of them
+    assert _chains_of(net, (2, 32, 14, 14)) == [True] * 3 + [False] + [True] * 2
+    net = TwoChains(nn.Sequential(nn.Conv2d(64, 64, 1), nn.Conv2d(64, 64, 3, 2, 1)), _pair(64, False), 64)
+    net = net.to(torch.bfloat16)
+    assert _chains_of(net, (40, 64, 56, 56)) == [False] * 5       # 28 x 28: whole planes, large copies
+    assert _chains_of(net, (40, 64, 54, 54)) == [True] * 2 + [False] + [True] * 2   # 27 x 27
+
+
+def test_a_copy_counts_once_for_all_its_readers():
+    """1.6 MB read by two convolutions is a small copy, although its readers read 3.2 MB."""
+
+    class Fork(nn.Module):
+        def __init__(self):
+            super().__init__()
+            self.a, self.b, self.c = (nn.Conv2d(i, o, 1) for i, o in ((64, 32), (64, 32), (32, 64)))
+
+        def forward(self, x):
+            return self.c(self.a(x) + self.b(x))
+
+    m = cs.swap_backend(Fork().to(torch.bfloat16), "implicit_gemm")
+    m._native.plan(16, 64, 28, 28)
+    assert m._native.describe().count("channels_last") == 3
+
+
+@pytest.mark.parametrize("dtype,width,expected", [("bf16", 56, 0), ("bf16", 60, 3), ("bf16", 14, 3), ("f32", 56, 3)])
+def test_depthwise_chains_by_row_width(dtype, width, expected):
+    """bf16 depthwise layers on rows of whole 16 bytes are as fast on planes."""
+    net = nn.Sequential(nn.Conv2d(24, 144, 1), nn.Conv2d(144, 144, 3, 1, 1, groups=144), nn.Conv2d(144, 24, 1))
+    m = cs.swap_backend(net.to(variants.DTYPES[dtype]), ["implicit_gemm", "direct", "implicit_gemm"])
+    m._native.plan(8, 24, width, width)
+    assert m._native.describe().count("channels_last") == expected
