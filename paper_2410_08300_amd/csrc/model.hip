@@ -167,7 +167,7 @@ template <bool MAX>
 __global__ __launch_bounds__(256) void pool3s2_to_nhwc_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ y,
                                                               int C, int H, int W, int P, int Q, int qtiles,
                                                               int ctiles) {
-  __shared__ uint16_t tile[32 * 72];  // [column][channel], rows of 72 values
+  __shared__ __align__(16) uint16_t tile[32 * 72];  // [column][channel], rows of 72 values (nine 16-byte units)
   int b = blockIdx.x;
   const int qt = b % qtiles;
   b /= qtiles;
