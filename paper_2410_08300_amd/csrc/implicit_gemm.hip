@@ -185,9 +185,11 @@ __global__ __launch_bounds__(kThreads) void implicit_gemm_kernel(IgArgs a) {
   }
   // Element e of the unit loaded for chunk offset c0: scalar (wave-uniform)
   // channel offset c0 + e; in the tail chunk, where the unit may run past the
-  // group's channels, lanes past it use the out-of-range offset (zero).
+  // group's channels, lanes past it use the out-of-range offset (zero).  The
+  // scalar offset itself stays on the group's last channel there: the range
+  // check is made against the buffer's size less that offset.
   auto load_unit_elem = [&](uint32_t voff, int cgb, int c0, int e) -> uint32_t {
-    const uint32_t so = static_cast<uint32_t>((c0 + e) * HW * ES);
+    const uint32_t so = static_cast<uint32_t>(min(c0 + e, a.Cg - 1) * HW * ES);
     const bool tail = c0 + UE * NG > a.Cg;  // uniform
     const uint32_t vo = (tail && cgb + c0 + e >= a.Cg) ? a.x_bytes : voff;
     return buf_load_elem(xr, vo, so, (T*)nullptr);

@@ -120,8 +120,9 @@ __global__ __launch_bounds__(2 * kThreads) void implicit_ws_kernel(WsArgs a) {
     // (c0 + e) * plane: the second part is the same for every lane, so it
     // goes into the load's scalar offset and the per-lane offset stays fixed
     // for the whole tile.  Only the last, partial chunk checks channels per
-    // lane.  An item outside the image has offset x_bytes, which stays past
-    // the buffer's end whatever is added.
+    // lane.  An item outside the image has offset x_bytes, past the end of
+    // the buffer as long as the scalar offset is within it: it stays on the
+    // last channel where a chunk's channels end before its sixteenth.
     auto issue_halo = [&](int ch) {
       const int c0 = (ch_begin + ch) * 16;
       const bool tail = c0 + 16 > a.C;
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(2 * kThreads) void implicit_ws_kernel(WsArgs a) {
         if (t < a.nh) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            const uint32_t so = static_cast<uint32_t>(c0 + e) * plane;
+            const uint32_t so = static_cast<uint32_t>(min(c0 + e, a.C - 1)) * plane;
             uint32_t vo = hvo[t];
             if (tail && c0 + hcg[t] * 8 + e >= a.C) vo = a.x_bytes;
             if constexpr (PAIR)
