@@ -71,15 +71,9 @@ struct NhArgs {
 
 __device__ __forceinline__ uint32_t magic_div(uint32_t e, uint32_t m) { return m ? __umulhi(e, m) : e; }
 
-template <typename T>
-__device__ __forceinline__ void nh_mfma(f32x16_t& acc, const vec16& a, const vec16& b) {
-  mfma_32x32<T>(acc, a, b);
-}
-
 // Residual add and ReLU on one 16-byte unit of output values already rounded to T.
 template <typename T>
-__device__ __forceinline__ void nh_finish(vec16& v, const vec16& r, bool has_res, int relu) {
-  if (!has_res) return;
+__device__ __forceinline__ void nh_finish(vec16& v, const vec16& r, int relu) {
   if constexpr (sizeof(T) == 2) {
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
@@ -139,7 +133,7 @@ __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
   // contiguous ranges, so the tiles that read the same pixels share an L2.
   const int per_xcd = (a.units + 7) >> 3;
   const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (unit >= a.units || static_cast<int>(blockIdx.x >> 3) >= per_xcd) return;  // uniform
+  if (unit >= a.units) return;  // uniform
   const int jt = unit / a.nit;
   const int j0 = jt * TJ, i0 = (unit - jt * a.nit) * TI;
   const u32x4_t xr = dma_rsrc(a.x, a.x_bytes), wr = dma_rsrc(a.w, a.w_bytes);
@@ -333,8 +327,8 @@ __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) {
           f32x16_t& sum = BLOCKED ? part[mj][ni] : acc[mj][ni];
-          if constexpr (OUTC) nh_mfma<T>(sum, ff[t & 1][ni], fp[t & 1][mj]);
-          else nh_mfma<T>(sum, fp[t & 1][mj], ff[t & 1][ni]);
+          if constexpr (OUTC) mfma_32x32<T>(sum, ff[t & 1][ni], fp[t & 1][mj]);
+          else mfma_32x32<T>(sum, fp[t & 1][mj], ff[t & 1][ni]);
         }
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -451,7 +445,7 @@ __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
 #pragma unroll
         for (int it = 0; it < PASSES; ++it) r[it] = RPI * it < left ? load16(res + o0 + it * step) : vec16_zero();
 #pragma unroll
-        for (int it = 0; it < PASSES; ++it) nh_finish<T>(d[it], r[it], true, a.relu);
+        for (int it = 0; it < PASSES; ++it) nh_finish<T>(d[it], r[it], a.relu);
       }
 #pragma unroll
       for (int it = 0; it < PASSES; ++it)
@@ -473,7 +467,7 @@ __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
             if (RPI * it < left) __builtin_memcpy(&r[it], res + o0 + it * step, 16);
           }
 #pragma unroll
-          for (int it = 0; it < PASSES; ++it) nh_finish<T>(d[it], r[it], true, a.relu);
+          for (int it = 0; it < PASSES; ++it) nh_finish<T>(d[it], r[it], a.relu);
         }
 #pragma unroll
         for (int it = 0; it < PASSES; ++it)  // (the caller's tensor: element alignment)
@@ -498,7 +492,7 @@ __global__ __launch_bounds__(256 * Tl::G) void nhwc_conv_kernel(NhArgs a) {
               if (RPI * it < left && in[h]) __builtin_memcpy(&r[it].d[2 * h], res + o[h] + it * step, 8);
           }
 #pragma unroll
-          for (int it = 0; it < PASSES; ++it) nh_finish<T>(d[it], r[it], true, a.relu);
+          for (int it = 0; it < PASSES; ++it) nh_finish<T>(d[it], r[it], a.relu);
         }
 #pragma unroll
         for (int it = 0; it < PASSES; ++it)
@@ -835,6 +829,8 @@ bool nhwc_applies(const Shape& s) {
   // Offsets are 32-bit byte offsets below 2^31 from the (padding-shifted) base.
   if ((s.N * s.H * s.W + s.ph * s.W + s.pw + (s.R * s.dh + 1) * s.W + s.S * s.dw) * cu * 16 >= lim) return false;
   if (s.K * s.R * s.S * cu * 16 >= lim) return false;
+  // The copy's workgroups (64 pixels of one image, 8 units) of 256 threads: a grid holds fewer than 2^32 threads.
+  if (s.N * ((s.H * s.W + 63) / 64) * ((cu + 7) / 8) >= (int64_t)1 << 24) return false;
   return s.R * s.S * cu < 65536 && s.N * s.P * s.Q + 128 < lim;
 }
 

@@ -412,3 +412,12 @@ def test_depthwise_chains_by_row_width(dtype, width, expected):
     m = cs.swap_backend(net.to(variants.DTYPES[dtype]), ["implicit_gemm", "direct", "implicit_gemm"])
     m._native.plan(8, 24, width, width)
     assert m._native.describe().count("channels_last") == expected
+
+
+@pytest.mark.parametrize("images,expected", [((1 << 24) - 1, 3), (1 << 24, 0)])
+def test_copies_of_more_workgroups_than_a_grid_holds_stay_planes(images, expected):
+    """One workgroup of 256 threads copies an image of up to 64 pixels; a grid has fewer than 2^32 threads."""
+    net = nn.Sequential(nn.Conv2d(8, 8, 1), nn.Conv2d(8, 8, 3, 1, 1, groups=8), nn.Conv2d(8, 8, 1))
+    m = cs.swap_backend(net.to(torch.bfloat16), ["implicit_gemm", "direct", "implicit_gemm"])
+    m._native.plan(images, 8, 2, 1)
+    assert m._native.describe().count("channels_last") == expected
