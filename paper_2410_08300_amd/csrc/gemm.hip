@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(GemmArgs g, int njt, int 
   const int units = njt * nit * g.batch;
   const int per_xcd = (units + 7) >> 3;
   const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (unit >= units || static_cast<int>(blockIdx.x >> 3) >= per_xcd) return;  // uniform
+  if (unit >= units) return;  // uniform
   const int jt = unit / nit;
   const int b = jt / njt;
   const int j0 = (jt - b * njt) * TJ, i0 = (unit - jt * nit) * TI;

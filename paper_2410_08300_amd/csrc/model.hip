@@ -110,9 +110,6 @@ __global__ __launch_bounds__(256) void global_avgpool_kernel(const T* __restrict
 
 // ---- the same on channels-last values (channels whole 16-byte units) ------
 
-__device__ __forceinline__ float bf16_at(const vec16& v, int i) {
-  return __uint_as_float((i & 1) ? (v.d[i >> 1] & 0xffff0000u) : (v.d[i >> 1] << 16));
-}
 template <typename T>
 __device__ __forceinline__ float unit_at(const vec16& v, int i) {
   return elem<T>::to_f32(convsel::vec16_get<T>(v, i));
@@ -203,7 +200,7 @@ __global__ __launch_bounds__(256) void pool3s2_to_nhwc_kernel(const bf16_t* __re
   }
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
-    auto at = [&](int i) { return i < 0 ? left[r] : i < 8 ? bf16_at(lo[r], i) : bf16_at(hi[r], i - 8); };
+    auto at = [&](int i) { return i < 0 ? left[r] : i < 8 ? unit_at<bf16_t>(lo[r], i) : unit_at<bf16_t>(hi[r], i - 8); };
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
