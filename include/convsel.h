@@ -115,6 +115,10 @@ conv_status_t conv2d_check(const conv2d_desc_t* desc, conv_algo_t algo);
  *    for common layers), plus, for layers whose output tiles alone would
  *    leave compute units idle, S*N*K*P*Q fp32 partial sums of a channel
  *    split over S <= 8 workgroups (summed by a second, deterministic kernel).
+ *    bf16 layers that run channels-last instead (5 x 5, 7 x 7, dilated or
+ *    ragged; conv2d_describe says which) need the filters with their channels
+ *    innermost and a channels-last copy of a batch of images: together at
+ *    most 32 MiB.  With a prebuilt package the copy remains.
  *  - implicit precomputed-index GEMM: its package (zero-padded filters, one
  *    8-byte table entry per reduction index and per output pixel of a launch).
  *  - IM2COL + GEMM and Winograd: the column matrix / transformed tiles, built

@@ -35,7 +35,9 @@
  *      operand exists before that convolution runs is fused into it: the
  *      convolution's epilogue adds the other operand and applies the add's
  *      ReLU, y = relu(round(conv + b) + other), and the add launches
- *      nothing.  Host only.
+ *      nothing.  Intermediate values may be held channels-last (N x H x W x C)
+ *      where all their readers and writers can; x and y never are.  A copy of
+ *      x made for that is an intermediate value of the arena.  Host only.
  *   3. convsel_model_bind(arena): the caller provides the arena (at least the
  *      planned bytes, 256-byte aligned); the library packs every filter and
  *      copies every bias into it, on `stream`.

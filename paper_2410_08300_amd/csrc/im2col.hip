@@ -220,8 +220,9 @@ bool im2col_tile(const Shape& s, Im2colTile& t) {
 }
 
 // The same matrix for the remaining layers whose rows are whole units
-// (im2col_route): one thread per 16-byte unit of a row, consecutive threads along the row; the UE
-// input elements are gathered with the tap indices stepped incrementally.
+// (im2col_route): one thread per 16-byte unit of a row, consecutive threads along
+// the row; the UE input elements are gathered with the tap indices stepped
+// incrementally.
 template <typename T>
 __global__ __launch_bounds__(256) void im2col_vec_kernel(Im2colArgs a, int64_t units) {
   constexpr int UE = elem<T>::per16;

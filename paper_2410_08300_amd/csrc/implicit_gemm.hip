@@ -1793,17 +1793,20 @@ std::string describe_typed(const Shape& s) {
 
 namespace {
 // bf16 layers that go to the channels-last kernel (a transposing copy of the
-// input, then the DMA kernel), measured prepacked against the kernel each would
-// take otherwise, 90 random layers:
+// input, then the DMA kernel), with their time over that of the kernel they would
+// take otherwise, prepacked (1180 random layers):
 //  * instead of implicit_gemm_kernel (5 x 5, 7 x 7, dilated or strided 3 x 3
-//    filters): 0.93 to 3.7 times as fast, median 1.5 (5 x 5, stride 2, 256 ->
-//    256 of 28 x 28, 128 images: 211 -> 135 us); not for strided 3 x 3 filters
-//    with at most 8 channels, 0.67 to 0.94, whose copy pads channels and holds
-//    four times the pixels that are read;
-//  * instead of implicit_ws_kernel (3 x 3): 1.1 to 1.5 with fewer than 64
-//    channels, of which that kernel's chunks pad most, and for small layers
-//    below 128 channels, which it splits and reduces; 0.6 to 0.9 with more,
-//    where its own channel split fills the chip better.
+//    filters; 865 layers): 0.15 to 2.5, 0.60 in the geometric mean (5 x 5, stride
+//    2, 256 -> 256 of 28 x 28, 128 images: 211 -> 136 us).  56 of them are slower by
+//    more than 5 percent: strided layers with few filters whose copy is tens of
+//    MB; no line in sizes was found that takes these out and leaves those that
+//    gain.  Strided 3 x 3 filters with at most 8 channels, whose copy pads channels
+//    and holds four times the pixels that are read, are: they took 1.06 to 1.5;
+//  * instead of implicit_ws_kernel (3 x 3; 315 layers): 0.83 to 0.89 in the
+//    geometric mean of two runs, at most 1.5, and 0.71 with the package built in the call (up to four
+//    channels 0.80); with fewer than 64 channels, of which that kernel's chunks pad
+//    most, and for small layers below 128 channels, which it splits and reduces.
+//    With more channels 1.1 to 1.7, its own channel split fills the chip better.
 // Below 4 MFLOP both are a few launches and nothing else.
 bool use_nhwc(const Shape& s) {
   if (s.dtype != DT_BF16 || use_pointwise(s) || rows_applies(s) || k3_applies(s)) return false;

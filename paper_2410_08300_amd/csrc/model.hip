@@ -480,14 +480,15 @@ conv_algo_t default_of(const conv2d_desc_t& d) {
 // Channels-last planning.  An implicit GEMM convolution (one group, C and K whole
 // 16-byte units) can run the channels-last kernel, which needs no transposition
 // of its input, and a direct depthwise 3 x 3 layer one of its own; a value
-// between two such operations is then held as N x H x W x C.  A value qualifies when everything that writes or reads it
-// can handle that: those convolutions, pooling, global average pooling, and
-// adds and ReLUs whose values all qualify; flattens only of 1 x 1 planes,
-// where the two layouts are the same.  The model's input and output stay N x C
-// x H x W; a convolution on either end reads a channels-last copy of its input
-// (one copy per value, made by a transposing pass) or writes N x K x P x Q
-// itself.  A convolution with no such neighbour keeps the kernels of its own:
-// the transposing pass alone would cost more than it gains.
+// between two such operations is then held as N x H x W x C.  A value qualifies
+// when everything that writes or reads it can handle that: those convolutions,
+// pooling, global average pooling, and adds and ReLUs whose values all qualify;
+// flattens only of 1 x 1 planes, where the two layouts are the same.  The
+// model's input and output stay N x C x H x W; a convolution on either end reads
+// a channels-last copy of its input (one copy per value, made by a transposing
+// pass) or writes N x K x P x Q itself.  A convolution with no such neighbour
+// keeps the kernels of its own: the transposing pass alone would cost more than
+// it gains.
 void plan_layouts(convsel_model& m, int out_root) {
   const int nv = (int)m.vals.size();
   for (Value& v : m.vals) {

@@ -717,6 +717,10 @@ uint32_t magic_of(int d) { return d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) 
 // at batch 32, each run with every tile; median error 3 to 5 percent).  The
 // sum over those layers with the tile this picks is 812 us; 811 with the best
 // measured one for each, 870 with the best single tile.
+// On layers it was not fitted to (220 random ones, bf16, 3 x 3 to 7 x 7, 9 to 512
+// channels, copy included): 1.04 times the best tile's time in the geometric mean,
+// 1.65 at worst; in sum 5.24 ms, with the best tile of each 4.88, with the best
+// single tile 7.17.
 // In fp32 the matrix instructions bound a k-tile (a sixteenth of the bf16 rate):
 // mfma32 is what one takes on a CU to itself.
 struct NhConfig {

@@ -134,11 +134,12 @@ int wino_row_blocks(int TQ, int lpr) { return (TQ + lpr / 2 - 2) / (lpr / 2 - 1)
 // least LDS each (240 random inputs: within 5 percent of the best width in bf16
 // and for few channels or tiles, where 32 and 64 lanes take up to twice as
 // long: 5 channels of 54 x 54, two images, 2.7, 3.8 and 5.3 us).  In fp32, with more
-// than a block of channels, blocks that they mostly fill and 2400 workgroups at 16 lanes, V's 128-byte rows are
-// what bounds it, and longer runs of them help: 32 lanes (219 channels of 18 x 19,
-// 26 images, 15.0 -> 12.5 us), or 64 where these leave no more lanes without a tile
-// and V (14 KB for seven tiles) stays below 430 MB (297 of 46 x 47, 10 images: 58.7, 40.5 and 35.6;
-// but 343 of 56 x 56, 36 images: 279, 252 and 364).
+// than a block of channels, blocks that they mostly fill and 2400 workgroups at 16
+// lanes, V's 128-byte rows are what bounds it, and longer runs of them help: 32
+// lanes (219 channels of 18 x 19, 26 images, 15.0 -> 12.5 us), or 64 where these
+// leave no more lanes without a tile and V (14 KB for seven tiles) stays below 430
+// MB (297 of 46 x 47, 10 images: 58.7, 40.5 and 35.6; but 343 of 56 x 56, 36
+// images: 279, 252 and 364).
 int wino_input_lanes(const Shape& s, int64_t nb) {
   const int TP = (int)((s.P + 1) / 2), TQ = (int)((s.Q + 1) / 2);
   const int64_t blocks = nb * TP * wino_row_blocks(TQ, 16) * ((s.C + CB - 1) / CB);

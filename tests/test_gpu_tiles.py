@@ -341,8 +341,8 @@ class Inverted(torch.nn.Module):
         return self.d(y) if self.more else y
 
 
-# N, C, mid, K, H, W, stride, pad, residual, further layer.  Depthwise strips of 2 x 4 (stride 1) and 1 x 4 (stride 2)
-# outputs with remainders, no padding and padding 2, one-row planes; fp32 tiles of the channels-last kernel.
+# N, C, mid, K, H, W, stride, pad, residual, further layer.  Depthwise strips of 2 x 4 and 2 x 7 (stride 1), 1 x 4 and
+# 1 x 7 (stride 2) outputs with remainders, no padding and padding 2, one-row planes; float32 layers channels-last.
 INVERTED = [
     (2, 16, 40, 16, 7, 9, 1, 1, True, False),
     (1, 8, 24, 16, 8, 5, 2, 1, False, True),
