@@ -1796,16 +1796,17 @@ namespace {
 // input, then the DMA kernel), with their time over that of the kernel they would
 // take otherwise, prepacked (1180 random layers):
 //  * instead of implicit_gemm_kernel (5 x 5, 7 x 7, dilated or strided 3 x 3
-//    filters; 865 layers): 0.15 to 2.5, 0.60 in the geometric mean (5 x 5, stride
-//    2, 256 -> 256 of 28 x 28, 128 images: 211 -> 136 us).  56 of them are slower by
-//    more than 5 percent: strided layers with few filters whose copy is tens of
-//    MB; no line in sizes was found that takes these out and leaves those that
+//    filters; 865 layers): 0.16 to 2.5, 0.61 in the geometric mean (5 x 5, stride
+//    2, 256 -> 256 of 28 x 28, 128 images: 211 -> 137 us).  76 of them are slower by
+//    more than 5 percent, most of them strided with few filters and a copy of tens
+//    of MB; no line in sizes was found that takes these out and leaves those that
 //    gain.  Strided 3 x 3 filters with at most 8 channels, whose copy pads channels
 //    and holds four times the pixels that are read, are: they took 1.06 to 1.5;
-//  * instead of implicit_ws_kernel (3 x 3; 315 layers): 0.83 to 0.89 in the
-//    geometric mean of two runs, at most 1.5, and 0.71 with the package built in the call (up to four
-//    channels 0.80); with fewer than 64 channels, of which that kernel's chunks pad
-//    most, and for small layers below 128 channels, which it splits and reduces.
+//  * instead of implicit_ws_kernel (3 x 3; 315 layers): 0.38 to 1.5, 0.83 in the
+//    geometric mean (up to four channels 0.82; 51 slower by more than 5 percent),
+//    0.71 with the package built in the call (4 of them); with fewer than 64
+//    channels, of which that kernel's chunks pad most, and for small layers below
+//    128 channels, which it splits and reduces.
 //    With more channels 1.1 to 1.7, its own channel split fills the chip better.
 // Below 4 MFLOP both are a few launches and nothing else.
 bool use_nhwc(const Shape& s) {
