@@ -57,6 +57,8 @@ struct WsArgs {
   EpiArgs e;
 };
 
+enum WsLoads { WS_PIXELS, WS_WORDS, WS_HALVES };
+
 __device__ __forceinline__ int ws_vrow(int j, const WsArgs& a) {
   const int PQ = a.P * a.Q;
   const int n = j / PQ, pq = j - n * PQ;
@@ -64,10 +66,12 @@ __device__ __forceinline__ int ws_vrow(int j, const WsArgs& a) {
 }
 
 // PAIR: the halo is read as pixel pairs (W even: a pair at an even input
-// column is one aligned 32-bit word per channel); otherwise pixel by pixel.
+// column is one aligned 32-bit word per channel, or, with WS_HALVES, two 16-bit
+// loads for an input of 2-byte alignment); otherwise pixel by pixel.
 // MW: 32-row filter fragments per compute wave (its rows: 32 MW).
-template <int BM, bool PAIR, int MW>
+template <int BM, WsLoads LOADS, int MW>
 __global__ __launch_bounds__(2 * kThreads) void implicit_ws_kernel(WsArgs a) {
+  constexpr bool PAIR = LOADS != WS_PIXELS;
   extern __shared__ __align__(16) vec16 smem[];
   char* lds = reinterpret_cast<char*>(smem);
 
@@ -134,8 +138,12 @@ __global__ __launch_bounds__(2 * kThreads) void implicit_ws_kernel(WsArgs a) {
             const uint32_t so = static_cast<uint32_t>(min(c0 + e, a.C - 1)) * plane;
             uint32_t vo = hvo[t];
             if (tail && c0 + hcg[t] * 8 + e >= a.C) vo = a.x_bytes;
-            if constexpr (PAIR)
+            if constexpr (LOADS == WS_WORDS)
               hd[t][e] = __builtin_amdgcn_raw_buffer_load_b32(xr, vo, so, 0);
+            else if constexpr (LOADS == WS_HALVES)
+              hd[t][e] = static_cast<uint16_t>(__builtin_amdgcn_raw_buffer_load_b16(xr, vo, so, 0)) |
+                         static_cast<uint32_t>(static_cast<uint16_t>(
+                             __builtin_amdgcn_raw_buffer_load_b16(xr, vo + 2, so, 0))) << 16;
             else
               hd[t][e] = __builtin_amdgcn_raw_buffer_load_b16(xr, vo, so, 0);
           }
@@ -406,9 +414,9 @@ bool make_ws_plan(const Shape& s, WsPlan& pl, int64_t N1 = -1) {
   return true;
 }
 
-template <int BM, bool PAIR, int MW>
-hipError_t ws_launch(const WsPlan& pl, const WsArgs& a, hipStream_t stream) {
-  const auto kern = implicit_ws_kernel<BM, PAIR, MW>;
+template <int BM, WsLoads LOADS, int MW>
+hipError_t ws_launch_loads(const WsPlan& pl, const WsArgs& a, hipStream_t stream) {
+  const auto kern = implicit_ws_kernel<BM, LOADS, MW>;
   // Raise the dynamic-LDS limit once (calls may be captured into a graph
   // after the first one).
   static std::atomic<int> lds_limit{64 * 1024};
@@ -427,6 +435,15 @@ hipError_t ws_launch(const WsPlan& pl, const WsArgs& a, hipStream_t stream) {
                      a.e.partial, reinterpret_cast<const bf16_t*>(a.e.b), reinterpret_cast<bf16_t*>(a.e.y), total,
                      a.e.slab, a.P * a.Q, a.K, a.e.splits, a.e.relu, reinterpret_cast<const bf16_t*>(a.e.res));
   return hipGetLastError();
+}
+
+// Pairs are 32-bit words where the input is so aligned.  The plan's halo items
+// are pairs in either case.
+template <int BM, int MW>
+hipError_t ws_launch(const WsPlan& pl, const WsArgs& a, hipStream_t stream) {
+  if (!pl.pair) return ws_launch_loads<BM, WS_PIXELS, MW>(pl, a, stream);
+  return reinterpret_cast<uintptr_t>(a.x) % 4 == 0 ? ws_launch_loads<BM, WS_WORDS, MW>(pl, a, stream)
+                                                   : ws_launch_loads<BM, WS_HALVES, MW>(pl, a, stream);
 }
 
 }  // namespace
@@ -484,13 +501,7 @@ hipError_t ws_main(const Shape& s, const void* x, const void* wp, const void* b,
     a.e.b = b;
     a.e.partial = reinterpret_cast<float*>(part_ws);
     a.e.vec = store_piece(s, a.e.y);
-    // Pairs of pixels are read as aligned 32-bit words.
-    const bool pair = cur.pair && reinterpret_cast<uintptr_t>(a.x) % 4 == 0;
-    hipError_t e;
-    if (cur.BM == 64)
-      e = pair ? ws_launch<64, true, 1>(cur, a, stream) : ws_launch<64, false, 1>(cur, a, stream);
-    else
-      e = pair ? ws_launch<128, true, kWsMW128>(cur, a, stream) : ws_launch<128, false, kWsMW128>(cur, a, stream);
+    const hipError_t e = cur.BM == 64 ? ws_launch<64, 1>(cur, a, stream) : ws_launch<128, kWsMW128>(cur, a, stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -460,6 +460,47 @@ def test_3x3_unaligned_filters(C):
     assert rel_err(f64(y), ref) <= tolerance("bf16", "implicit_gemm")
 
 
+# N, C, H, W, K, R, stride, pad, groups, algorithm, kernel that the layer runs: layers whose input starts one element
+# past a 16-byte boundary (bf16: odd, so that no pair of pixels is an aligned word).
+UNALIGNED = [
+    (5, 13, 2, 12, 46, 3, (2, 1), (3, 0), 1, "implicit_gemm", "implicit_ws_kernel<64,1,1>"),
+    (4, 40, 16, 22, 3, 3, 1, (3, 1), 1, "implicit_gemm", "implicit_ws_kernel<64,1,1>"),
+    (2, 130, 10, 12, 200, 3, 1, 1, 1, "implicit_gemm", "implicit_ws_kernel<128,1,1>"),
+    (2, 130, 10, 11, 200, 3, 1, 1, 1, "implicit_gemm", "implicit_ws_kernel<128,0,1>"),
+    (3, 32, 9, 12, 48, 3, 1, 1, 1, "implicit_gemm", "conv3x3_kernel"),
+    (3, 32, 9, 6, 48, 3, 2, 1, 1, "implicit_gemm", "conv3x3_kernel"),
+    (2, 64, 14, 14, 128, 3, 1, 1, 1, "implicit_gemm", "conv3x3_kernel"),
+    (2, 24, 12, 12, 40, 5, 1, 2, 1, "implicit_gemm", "nhwc_conv_kernel"),
+    (2, 3, 24, 32, 16, 7, 2, 3, 1, "implicit_gemm", "implicit_rows_kernel"),
+    (2, 24, 12, 12, 40, 3, 1, 1, 2, "implicit_gemm", "implicit_gemm_kernel"),
+    (2, 48, 14, 16, 48, 3, 1, 1, 48, "direct", "direct_dw3_kernel"),
+    (2, 48, 13, 15, 48, 3, 2, 1, 48, "direct", "direct_dw3_kernel"),
+    (2, 24, 12, 12, 40, 3, 1, 1, 1, "winograd", "wino_input_kernel"),
+    (2, 24, 12, 12, 40, 3, 1, 1, 1, "im2col_gemm", "im2col"),
+]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("case", UNALIGNED, ids=str)
+def test_unaligned_input(case, dtype):
+    """An input needs its elements' alignment only, and nothing next to it counts."""
+    N, C, H, Wd, K, R, st, pad, G, algo, kernel = case
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(W.seed_for(31, C, K))
+    x = torch.randn(N, C, H, Wd, generator=g).to(dt)
+    w = (torch.randn(K, C // G, R, R, generator=g) * (2.0 / (C // G * R * R)) ** 0.5).to(dt)
+    if dtype == "bf16":
+        assert kernel in cs.describe((N, C, H, Wd), w.shape, st, pad, 1, G, dt, algo)
+    buf = torch.full((x.numel() + 2,), float("nan"), dtype=dt, device=DEV)   # also outside the input
+    xd = buf[1:-1].view(x.shape)
+    xd.copy_(x)
+    assert xd.data_ptr() % 16 == x.element_size()
+    say("case unaligned input", case, dtype)
+    y = cs.conv2d(xd, w.to(DEV), None, st, pad, 1, G, algo=algo)
+    torch.cuda.synchronize()
+    assert rel_err(f64(y), oracle.conv2d(f64(x), f64(w), None, st, pad, 1, G, False)) <= tolerance(dtype, algo)
+
+
 # Every byte a call writes must lie in y or in its workspace: the operands
 # and the workspace sit in one buffer between guard bands of a fill pattern,
 # and after the call the guards and the inputs must be unchanged.
